@@ -109,10 +109,10 @@ rt_status rt_dirset_destroy(rt_dirset* set);
  * RT_ERR_MESH) and the positions (finite, every coordinate of magnitude at most
  * 1e150 so that the walk's squared distances stay finite; error RT_ERR_ARG)
  * and synchronises on `stream` to read the verdict before anything is built.
- * Then builds a neighbour-record table (36 bytes per neighbour entry: position,
- * id, the neighbour's own row; each row sorted by id) that the tracer reads
- * instead of chasing nbr_idx into pos and nbr_off, with the rows laid out in
- * the Morton order of the points (computed on the host from a copy of the
+ * Then builds a table of rows (per point 32 bytes and per neighbour entry 16:
+ * the edge to it and where its own row lies, each row sorted by id, rounded up
+ * to whole units of 64 bytes) that the tracer reads instead of chasing nbr_idx
+ * into pos and nbr_off, with the rows laid out in the Morton order of the points (computed on the host from a copy of the
  * positions, which the handle keeps for the spatial orders of plans; 24 bytes
  * of host memory per point).  The order of a point's neighbours in nbr_idx and
  * the order of the points do not affect any result.  The positions and lists

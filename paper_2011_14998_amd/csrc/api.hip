@@ -315,17 +315,31 @@ rt_status rt::model_create(const double* pos, int64_t P, const int64_t* nbr_off,
     m->E = E;
     m->vel = vel;
     RT_HIP(hipGetDevice(&m->device));
-    int32_t* bad = nullptr;
-    hipError_t e = hipMalloc((void**)&m->nbr, sizeof(NbrRec) * (size_t)std::max<int64_t>(E, 1));
-    if (e == hipSuccess) e = hipMalloc((void**)&m->nid, sizeof(int32_t) * (size_t)std::max<int64_t>(E, 1));
-    if (e == hipSuccess) e = hipMalloc((void**)&m->rows, sizeof(int2) * (size_t)P);
-    if (e == hipSuccess) e = hipMalloc((void**)&bad, sizeof(int32_t));
-    if (e == hipSuccess) e = launch_fill_i32(bad, 1, 0, s);
-    if (e == hipSuccess) e = launch_check_model(m, bad, s);
-    int32_t hbad = 0;
-    if (e == hipSuccess) e = hipMemcpyAsync(&hbad, bad, sizeof(int32_t), hipMemcpyDeviceToHost, s);
+    m->row_bytes = plan_rows(m->tab, P, E);
+    int32_t* chk = nullptr;  // {bad bits, -, reach (64 bits)}
+    hipError_t e = hipMalloc((void**)&m->recs, m->row_bytes);
+    if (e == hipSuccess) e = hipMalloc((void**)&m->codes, sizeof(uint32_t) * (size_t)P);
+    if (e == hipSuccess) e = hipMalloc((void**)&chk, 4 * sizeof(int32_t));
+    if (e == hipSuccess) e = launch_fill_i32(chk, 4, 0, s);
+    if (e == hipSuccess) e = launch_check_model(m, chk, (uint64_t*)(chk + 2), s);
+    int32_t hchk[4] = {0, 0, 0, 0};
+    if (e == hipSuccess) e = hipMemcpyAsync(hchk, chk, sizeof(hchk), hipMemcpyDeviceToHost, s);
     if (e == hipSuccess) e = hipStreamSynchronize(s);
-    if (bad) (void)hipFree(bad);
+    if (chk) (void)hipFree(chk);
+    const int32_t hbad = hchk[0];
+    m->tab.recs = m->recs;
+    m->tab.code = m->codes;
+    {  // every coordinate times the scale is below 1 (a power of two: the products are exact)
+        double reach;
+        std::memcpy(&reach, hchk + 2, sizeof(reach));
+        int ex = 0;
+        if (reach > 0.0 && std::isfinite(reach)) (void)std::frexp(reach, &ex);
+        // within 2^+-40 FP32 holds edges and squared distances as they are
+        const double sc = std::abs(ex) <= 40 ? 1.0 : std::ldexp(1.0, -std::max(-1000, std::min(1000, ex)));
+        m->tab.scale = sc;
+        m->tab.floor_s = (float)(0x1p-120 + sc * 0x1p-1070);
+        m->tab.floor_D = (float)(0x1p-120 + sc * 0x1p-1070 + sc * (sc * 0x1p-1070));
+    }
     if (e == hipSuccess && !hbad) {  // a valid CSR: build the records
         // rows in the Morton order of the points, so that the rows a walk reads next are near
         // in memory (the positions' host copy is kept for the plans' origin orders)
@@ -343,24 +357,22 @@ rt_status rt::model_create(const double* pos, int64_t P, const int64_t* nbr_off,
             if (e == hipSuccess)
                 e = hipMemcpyAsync(lay_d, lay.data(), sizeof(int32_t) * (size_t)P, hipMemcpyHostToDevice, s);
         }
-        if (e == hipSuccess) e = hipMalloc(&ws, build_nbr_workspace(P));
-        if (e == hipSuccess) e = launch_build_nbr(m, key, lay_d, ws, s);
+        if (e == hipSuccess) e = hipMalloc(&ws, build_rows_workspace(P));
+        if (e == hipSuccess) e = launch_build_rows(m, key, lay_d, ws, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
         if (lay_d) (void)hipFree(lay_d);
         if (ws) (void)hipFree(ws);
     }
     if (e != hipSuccess) {
         rt_status st = hip_fail(e, "rt_model_create");
-        if (m->nbr) (void)hipFree(m->nbr);
-        if (m->nid) (void)hipFree(m->nid);
-        if (m->rows) (void)hipFree(m->rows);
+        if (m->recs) (void)hipFree(m->recs);
+        if (m->codes) (void)hipFree(m->codes);
         delete m;
         return st;
     }
     if (hbad) {
-        if (m->nbr) (void)hipFree(m->nbr);
-        if (m->nid) (void)hipFree(m->nid);
-        if (m->rows) (void)hipFree(m->rows);
+        if (m->recs) (void)hipFree(m->recs);
+        if (m->codes) (void)hipFree(m->codes);
         delete m;
         return fail(hbad == 8 ? RT_ERR_ARG : RT_ERR_MESH, std::string("rt_model_create: invalid model (") +
                                      ((hbad & 1) ? "index out of range " : "") + ((hbad & 2) ? "bad offsets " : "") +
@@ -373,9 +385,8 @@ rt_status rt::model_create(const double* pos, int64_t P, const int64_t* nbr_off,
 
 extern "C" rt_status rt_model_destroy(rt_model* m) {
     if (!m) return RT_OK;
-    if (m->nbr) (void)hipFree(m->nbr);
-    if (m->nid) (void)hipFree(m->nid);
-    if (m->rows) (void)hipFree(m->rows);
+    if (m->recs) (void)hipFree(m->recs);
+    if (m->codes) (void)hipFree(m->codes);
     delete m;
     return RT_OK;
 }

@@ -90,15 +90,33 @@ struct rt_dirset {
     const double* d_w2() const { return dev.w2; }
 };
 
-// One neighbour entry as the tracer reads it (32 bytes, two 16-byte loads): the
-// neighbour's position and its own CSR row (start, degree), so a step needs no
-// further load to continue from the chosen neighbour.  Rows are sorted by
-// neighbour id; the ids themselves sit in a separate array in the same order.
-struct alignas(16) NbrRec {
+namespace rt {
+// A point's row as the tracer reads it: the head, then a record per neighbour (ascending
+// id), in whole units of 64 bytes.
+struct alignas(16) RowHead {
     double x, y, z;
-    int32_t start;
-    int32_t deg;
+    int32_t id;
+    float longest;  // at least the longest edge of the row (scaled)
 };
+struct alignas(16) RowRec {
+    float ex, ey, ez;  // edge to the neighbour times the model's scale
+    uint32_t code;     // the neighbour's own row
+};
+static_assert(sizeof(RowHead) == 32 && sizeof(RowRec) == 16, "row layout");
+
+// Where the rows are: a row's code holds its start in units of 64 << sh bytes above nb bits
+// for its number of units of 64 (all ones: its first record's code is its degree).
+struct RowTab {
+    const char* recs = nullptr;
+    const uint32_t* code = nullptr;  // [P]
+    double scale = 1.0;              // a power of two that brings every coordinate below 1
+    float floor_s = 0.f, floor_D = 0.f;  // what underflow may move a projection and a squared distance by, scaled
+    int sh = 0, nb = 4;
+    __host__ __device__ uint64_t offset(uint32_t c) const { return (uint64_t)(c >> nb) << (6 + sh); }
+    __host__ __device__ int units(uint32_t c) const { return (int)(c & ((1u << nb) - 1)); }
+    __host__ __device__ bool more(uint32_t c) const { return (c & ((1u << nb) - 1)) == (1u << nb) - 1; }
+};
+}  // namespace rt
 
 struct rt_model {
     const double* pos = nullptr;
@@ -107,9 +125,10 @@ struct rt_model {
     const int32_t* idx = nullptr;
     int64_t E = 0;
     const float* vel = nullptr;
-    NbrRec* nbr = nullptr;  // owned: neighbour records, rows in Morton order of the points, each sorted by id
-    int32_t* nid = nullptr; // owned: the neighbour id of each record
-    int2* rows = nullptr;   // owned: per point {row start, degree}
+    char* recs = nullptr;      // owned: the rows, in Morton order of the points
+    uint32_t* codes = nullptr; // owned: each point's row code
+    rt::RowTab tab;
+    size_t row_bytes = 0;      // of recs
     int device = -1;
     // host copy of the positions, made on first need (spatial orders of plans); the
     // positions may not change while the handle lives
@@ -122,13 +141,15 @@ namespace rt {
 // ---------------------------------------------------------------- kernels (launchers)
 // trace.hip
 // Checks of a model's CSR and positions (bits of *bad: 1 index out of range, 2 bad offsets,
-// 4 self neighbour, 8 position not finite or beyond 1e150).
-hipError_t launch_check_model(const rt_model* m, int32_t* bad, hipStream_t s);
-// Records, ids and rows of a checked model: the rows laid out in the point order `lay`
-// (device [P], NULL: point order), each row in ascending key[id] (key NULL: ascending id);
-// ws: build_nbr_workspace(P) bytes.
-size_t build_nbr_workspace(int64_t P);
-hipError_t launch_build_nbr(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s);
+// 4 self neighbour, 8 position not finite or beyond 1e150); *reach: the bits of the largest
+// |coordinate| (both zeroed by the caller).
+hipError_t launch_check_model(const rt_model* m, int32_t* bad, uint64_t* reach, hipStream_t s);
+// Layout of the rows of a model (tab.sh, tab.nb) and the bytes they take.
+size_t plan_rows(RowTab& tab, int64_t P, int64_t E);
+// Rows of a checked model, laid out in the point order `lay` (device [P], NULL: point
+// order), each in ascending key[id] (key NULL: ascending id); ws: build_rows_workspace(P) bytes.
+size_t build_rows_workspace(int64_t P);
+hipError_t launch_build_rows(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s);
 // `order` (optional): spatially sorted permutation of origin positions; the
 // rays are then walked direction-major in that origin order.  gl: lanes per
 // ray, 4, 8 or 16 (anything else: 4).  `ray_order` (optional, n_rays origin

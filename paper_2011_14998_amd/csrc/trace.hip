@@ -10,16 +10,14 @@
 // q = fma(-Z, d, R) per axis, D = fma(q.z, q.z, fma(q.y, q.y, q.x q.x)).  Every
 // list is bit-identical to any other evaluation of the same rule.
 //
-// Data layout: neighbour records {x, y, z, row start, degree} (32 bytes, two
-// 16-byte loads) in CSR order with each row sorted by neighbour id, the ids in
-// a parallel array, and a per-point {row start, degree} table, all built once
-// per model, so a step reads one record per neighbour instead of an index, a
-// position and the next row's offsets; the lanes walking a ray (4 by default)
-// read a point's whole row (~15 records, ~500 contiguous bytes) per step.  The walk's loads are
-// limited by the vector memory instructions the L1 path serves per clock, so
-// a record is two loads, and a chosen neighbour's id is read only when its
-// list entry is stored.  The tables of a 50k-point Delaunay mesh (~28 MB)
-// stay in the Infinity cache.
+// Data layout: each point has one row, a 32-byte head {x, y, z in FP64, id, the
+// longest edge} followed by a 16-byte record per neighbour in ascending id:
+// the edge to it in FP32 and where its own row lies.  Rows take whole units of
+// 64 bytes, so the four lanes that walk a ray read a unit per load, the head
+// and the first two records with the first, and a step reads one row (~280
+// bytes on a Delaunay mesh) and nothing else; the rows of 50k points (~16 MB)
+// stay in the Infinity Cache.
+// The FP32 edges only rule candidates out: see k_trace.
 #include "rt_internal.h"
 
 #pragma clang fp contract(off)
@@ -30,52 +28,106 @@ namespace {
 
 constexpr int TRACE_BLOCK = 256;
 
-// The records' rows are laid out in the order `lay` (a permutation of the points; NULL:
-// point order): the row of point lay[q] is the q-th row in memory.  Degrees in that order:
-__global__ __launch_bounds__(256) void k_layout_deg(const int64_t* __restrict__ off, const int32_t* __restrict__ lay,
-                                                     int64_t P, int32_t* __restrict__ deg) {
+// Rows are laid out in the order `lay` (a permutation of the points; NULL: point order):
+// the row of point lay[q] is the q-th row in memory.  A row of `deg` neighbours takes
+// row_units(deg) units of 64 bytes (its records start half a unit in), rounded up to whole
+// units of 64 << sh.  A count that the low nb bits of a row code cannot hold is marked by all
+// ones there; such a row has its degree in the code field of a blank first record.
+__device__ inline bool row_counted(int64_t deg, int nb) { return (deg + 5) / 4 < ((int64_t)1 << nb) - 1; }
+__device__ inline int64_t row_units(int64_t deg, int nb) { return (deg + (row_counted(deg, nb) ? 5 : 6)) / 4; }
+
+__global__ __launch_bounds__(256) void k_layout_units(const int64_t* __restrict__ off, const int32_t* __restrict__ lay,
+                                                       int64_t P, int sh, int nb, int32_t* __restrict__ units) {
     const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (q >= P) return;
     const int64_t p = lay ? (int64_t)lay[q] : q;
-    deg[q] = (int32_t)(off[p + 1] - off[p]);
+    units[q] = (int32_t)((row_units(off[p + 1] - off[p], nb) + (1 << sh) - 1) >> sh);
 }
 
-// rows[lay[q]] = {start of the q-th row (scanned degrees), degree}
-__global__ __launch_bounds__(256) void k_layout_rows(const int64_t* __restrict__ start, const int32_t* __restrict__ deg,
-                                                      const int32_t* __restrict__ lay, int64_t P,
-                                                      int2* __restrict__ rows) {
+// A record that no ray can take (NaN edge).
+__device__ inline RowRec blank_rec(uint32_t code = 0) { return RowRec{NAN, 0.f, 0.f, code}; }
+
+// The table starts with ROW_BLANK units of such records: what a lane of the walk reads in
+// place of a record past its row's end.
+constexpr int ROW_BLANK = 8;
+
+__global__ void k_blank_rows(RowRec* __restrict__ recs, int n) {
+    const int i = blockIdx.x * blockDim.x + threadIdx.x;
+    if (i < n) recs[i] = blank_rec();
+}
+
+// code[lay[q]] = the q-th row's start (`first` + scanned units) above nb bits of its units
+__global__ __launch_bounds__(256) void k_layout_codes(const int64_t* __restrict__ start, const int64_t* __restrict__ off,
+                                                       const int32_t* __restrict__ lay, int64_t P, int nb,
+                                                       int64_t first, uint32_t* __restrict__ code) {
     const int64_t q = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     if (q >= P) return;
-    rows[lay ? (int64_t)lay[q] : q] = make_int2((int)start[q], deg[q]);
+    const int64_t p = lay ? (int64_t)lay[q] : q;
+    const int64_t deg = off[p + 1] - off[p];
+    const uint32_t u = row_counted(deg, nb) ? (uint32_t)row_units(deg, nb) : (1u << nb) - 1;
+    code[p] = ((uint32_t)(first + start[q]) << nb) | u;
 }
 
-// Point p's records at rows[p].x: each neighbour k's position and its own row (one thread
-// per point; the model has been checked, so every index is in range).
-__global__ __launch_bounds__(256) void k_build_nbr(const double* __restrict__ pos, int64_t P,
-                                                    const int64_t* __restrict__ off,
-                                                    const int32_t* __restrict__ idx, const int2* __restrict__ rows,
-                                                    NbrRec* __restrict__ nbr, int32_t* __restrict__ nid) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const int64_t a = off[p], d = rows[p].x;
-    const int n = rows[p].y;
-    for (int j = 0; j < n; ++j) {
+// Row of point p, BUILD_LANES lanes per point, each record placed by its rank in ascending
+// id, or in ascending key[id] when a key is given (equal keys in list order).  The walk
+// relies on that order: equal distances go to the earlier record.  The row's last unit is
+// filled up with blank records.  The model has been checked, so every index is in range.
+constexpr int BUILD_LANES = 16;
+
+__global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ pos, int64_t P,
+                                                     const int64_t* __restrict__ off,
+                                                     const int32_t* __restrict__ idx, const int32_t* __restrict__ key,
+                                                     const RowTab t, char* __restrict__ recs) {
+    const int64_t p = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / BUILD_LANES;
+    if (p >= P) return;  // whole groups leave together
+    const int sub = threadIdx.x & (BUILD_LANES - 1);
+    const int64_t a = off[p];
+    const int n = (int)(off[p + 1] - a);
+    char* row = recs + t.offset(t.code[p]);
+    const bool counted = row_counted(n, t.nb);
+    RowRec* rec = (RowRec*)(row + sizeof(RowHead)) + (counted ? 0 : 1);
+    const double x = pos[3 * p], y = pos[3 * p + 1], z = pos[3 * p + 2];
+    double longest = 0.0;
+    for (int j = sub; j < n; j += BUILD_LANES) {
         const int32_t k = idx[a + j];
-        NbrRec r;
-        r.x = pos[3 * (int64_t)k];
-        r.y = pos[3 * (int64_t)k + 1];
-        r.z = pos[3 * (int64_t)k + 2];
-        r.start = rows[k].x;
-        r.deg = rows[k].y;
-        nbr[d + j] = r;
-        nid[d + j] = k;
+        const int32_t kk = key ? key[k] : k;
+        int rank = 0;
+        for (int i = 0; i < n; ++i) {
+            const int32_t o = idx[a + i];
+            const int32_t ok = key ? key[o] : o;
+            rank += (ok < kk) || (ok == kk && i < j);
+        }
+        const double ex = (pos[3 * (int64_t)k] - x) * t.scale, ey = (pos[3 * (int64_t)k + 1] - y) * t.scale,
+                     ez = (pos[3 * (int64_t)k + 2] - z) * t.scale;
+        rec[rank] = RowRec{(float)ex, (float)ey, (float)ez, t.code[k]};
+        const double l = sqrt(ex * ex + ey * ey + ez * ez);
+        longest = l > longest ? l : longest;
+    }
+    const int filled = (int)(4 * row_units(n, t.nb)) - (counted ? 2 : 3);  // records that fit after rec[0]
+    for (int j = n + sub; j < filled; j += BUILD_LANES) rec[j] = blank_rec();
+#pragma unroll
+    for (int o = BUILD_LANES / 2; o > 0; o >>= 1) {
+        const double l = __shfl_xor(longest, o, BUILD_LANES);
+        longest = l > longest ? l : longest;
+    }
+    if (sub == 0) {
+        // never below the longest edge
+        *(RowHead*)row = RowHead{x, y, z, (int32_t)p, (float)(longest * 1.000001)};
+        if (!counted) rec[-1] = blank_rec((uint32_t)n);
     }
 }
 
 __global__ __launch_bounds__(256) void k_check_off(const int64_t* __restrict__ off, const int32_t* __restrict__ idx,
                                                     const double* __restrict__ pos, int64_t P, int64_t E,
-                                                    int32_t* __restrict__ bad) {
+                                                    int32_t* __restrict__ bad,
+                                                    unsigned long long* __restrict__ reach) {
     int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    // the largest |coordinate|, as bits (non-negative doubles order as integers), one atomic per wave
+    double far = 0.0;
+    if (p < P)
+        for (int i = 0; i < 3; ++i) far = fmax(far, fabs(pos[3 * p + i]));
+    for (int o = 32; o > 0; o >>= 1) far = fmax(far, __shfl_xor(far, o, 64));
+    if ((threadIdx.x & 63) == 0) atomicMax(reach, (unsigned long long)__builtin_bit_cast(uint64_t, far));
     if (p >= P) return;
     int64_t a = off[p], b = off[p + 1];
     if (a > b || a < 0 || b > E || (p == 0 && a != 0) || (p == P - 1 && b != E)) {
@@ -91,43 +143,44 @@ __global__ __launch_bounds__(256) void k_check_off(const int64_t* __restrict__ o
         if (!(fabs(pos[3 * p + i]) <= 1e150)) atomicOr(bad, 8);
 }
 
-// Each row's records in ascending neighbour id, or in ascending key[id] when a key is
-// given (insertion sort, one thread per row).  The walk's per-lane scan relies on it: a
-// lane meets its candidates in ascending id (key), so keeping the first of equal
-// distances keeps the smaller one.
-__global__ __launch_bounds__(256) void k_sort_rows(const int2* __restrict__ rows, int64_t P,
-                                                    NbrRec* __restrict__ nbr, int32_t* __restrict__ nid,
-                                                    const int32_t* __restrict__ key) {
-    int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= P) return;
-    const int64_t a = rows[p].x, b = a + rows[p].y;
-    for (int64_t e = a + 1; e < b; ++e) {
-        const NbrRec r = nbr[e];
-        const int32_t k = nid[e];
-        const int32_t kk = key ? key[k] : k;
-        int64_t f = e - 1;
-        while (f >= a && (key ? key[nid[f]] : nid[f]) > kk) {
-            nbr[f + 1] = nbr[f];
-            nid[f + 1] = nid[f];
-            --f;
-        }
-        nbr[f + 1] = r;
-        nid[f + 1] = k;
-    }
-}
-
-// GL lanes (4, 8 or 16) walk one ray.  At every step lane s takes neighbours s,
-// s+GL, ... of the current point's row (contiguous records sorted by id, so a
-// group reads whole cache lines and a lane meets its candidates in ascending
-// id; a lane's loads are issued four at a time) and keeps its best forward
-// candidate (least D, the first of equal D) together with that candidate's own CSR row (start,
-// degree, held in the record, so the next step's loads depend on nothing
-// else).  The group then finds the lexicographic minimum of (D, id) in two
-// DPP reductions (the minimum D, then the smallest id among the lanes that
-// reach it; stages: mirror within the row for 16 lanes, mirror within the
-// half-row for 8 or 16, then swap neighbours, then swap pairs), and every lane
-// reads the winner's Z and row from the one lane that holds it with a ballot
-// and ds_bpermute.  The result equals a sequential scan of the row.
+// GL lanes (4, 8 or 16) walk one ray.  At every step lane s takes candidates s,
+// s+GL, ... of the current point's row, their loads issued together (UW per
+// pass), and weighs them in FP32; the group combines its lanes in log2(GL) DPP
+// stages (mirror within the row for 16 lanes, mirror within the half-row for 8
+// or 16, then swap pairs, then swap neighbours).
+//
+// The choice is the FP64 rule's.  With p = R_c - Z_c d the current point's
+// offset from the axis and e the edge to candidate k, in real arithmetic
+//     Z_k - Z_c = s = e.d,     (offset of k from the axis) = p + e - s d,
+// so FP32 values of s and D = |p + e|^2 - s^2 come from the 16-byte record
+// alone, p (and the recorded Z) anew from the head's FP64 position at every
+// step.  With u = 2^-24, E the row's longest edge, A = |p|_1 + E and Rm =
+// |Z_c| + |p|_1 (at least |R_c|): rounding of e, d, p and of the chains moves s
+// by at most 5.2 u E and D by 19 u A^2, and the FP64 rule's own rounding moves
+// Z_k - Z_c by at most 2^-50 (Rm + E) and D_k by 2^-48 A Rm.  Hence
+//     tol_s = 8 u A + 2^-48 Rm,   tol_D = 10 A tol_s  (at least 64 u A^2 + 2^-45 A Rm)
+// plus floors for underflow (2^-120 for FP32's; on meshes of less than ~1e-140
+// also the FP64 rule's own, whose D may vanish: there it always decides), with
+// 2^-40 Rm added to A for edges near the resolution of the positions; edges are
+// scaled by a power of two so that every coordinate is below 1 where FP32's
+// range calls for it.  So a candidate with s < -tol_s is not forward, one with
+// s > tol_s is, and D orders two candidates when their FP32 values are more
+// than tol_D apart.  When no candidate lies between the two and the best
+// forward one is ahead of the second by more than tol_D, it is the FP64 rule's
+// choice; otherwise (about one step in 10^4 on irregular points; ties on
+// lattices) the group evaluates the rule itself in FP64 over the row
+// (exact_step).  The lists are those of the FP64 rule, bit for bit.
+//
+// What bounds it: VALU issue, ~170 instructions per step of a wave's 16 rays
+// (17 FP32 ones per candidate; the rule in FP64 takes ~20, most of them at
+// half rate), next to the row loads' latency (95 VGPRs, 5 waves per SIMD; 6
+// waves spill and are 3% slower).  Branch-free loads matter: lanes past their
+// row's end read blank records, and whether a wave takes a fifth or sixth
+// piece is a scalar branch; loads under exec masks made the compiler wait for
+// some before it issued the rest (7.9 ms).  50 000-point cloud, 96 pairs,
+// 2.6e8 steps: 5.5 ms (46e9 steps/s), against 9.4 ms with every candidate's
+// FP64 record (32 bytes) read and weighed; 26-neighbour grid, 5.0e8 steps: 9.8
+// ms against 16.3.
 //
 // List entries are buffered across the group and written in blocks of RUNL =
 // max(GL, 8) entries aligned to absolute list positions (ids 32 or 64 bytes, Z
@@ -139,6 +192,13 @@ __global__ __launch_bounds__(256) void k_sort_rows(const int2* __restrict__ rows
 // has completed (exactly one completes per RUNL steps); the first block of a
 // list is masked below its start, and when the ray ends the group stores what
 // is left (at most the two ring blocks).
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
+
+__device__ inline double make_f64(uint32_t lo, uint32_t hi) {
+    return __builtin_bit_cast(double, ((uint64_t)hi << 32) | lo);
+}
+
 enum TraceMode { TRACE_COUNT = 0, TRACE_WRITE = 1, TRACE_PADDED = 2 };
 
 
@@ -158,51 +218,70 @@ __device__ inline double dpp_d(double v) {
     return __builtin_bit_cast(double, p);
 }
 
-struct Cand {
-    double D, Z;
-    int32_t e, start, deg;  // e: record index (in a row sorted by id, the same order as the id)
-};
-
-template <int CTRL>
-__device__ inline int dpp_min_i(int v) {
-    const int o = dpp_i<CTRL>(v);
-    return o < v ? o : v;
-}
-
-template <int CTRL>
-__device__ inline double dpp_min_d(double v) {
-    return __builtin_fmin(v, dpp_d<CTRL>(v));
-}
-
-__device__ inline int bperm_i(int src_lane, int v) { return __builtin_amdgcn_ds_bpermute(src_lane << 2, v); }
-
-__device__ inline double bperm_d(int src_lane, double v) {
-    int2 p = __builtin_bit_cast(int2, v);
-    p.x = bperm_i(src_lane, p.x);
-    p.y = bperm_i(src_lane, p.y);
-    return __builtin_bit_cast(double, p);
-}
-
 constexpr int DPP_ROW_MIRROR = 0x140;   // lane i <-> 15-i within each 16 lanes
 constexpr int DPP_HALF_MIRROR = 0x141;  // lane i <-> 7-i within each 8 lanes
+constexpr int DPP_LANE0 = 0x00;         // quad_perm [0,0,0,0]
+constexpr int DPP_LANE1 = 0x55;         // quad_perm [1,1,1,1]
 constexpr int DPP_SWAP1 = 0xB1;         // quad_perm [1,0,3,2]
 constexpr int DPP_SWAP2 = 0x4E;         // quad_perm [2,3,0,1]
 
-// Minimum over the GL lanes of a group, left in every lane of it.
-template <int GL>
-__device__ inline double group_min_d(double v) {
-    if (GL == 16) v = dpp_min_d<DPP_ROW_MIRROR>(v);
-    if (GL >= 8) v = dpp_min_d<DPP_HALF_MIRROR>(v);
-    v = dpp_min_d<DPP_SWAP1>(v);
-    return dpp_min_d<DPP_SWAP2>(v);
+template <int CTRL, typename T>
+__device__ inline T dpp_t(T v) {  // a 32-bit value of another lane
+    return __builtin_bit_cast(T, dpp_i<CTRL>(__builtin_bit_cast(int, v)));
+}
+
+// Reductions over the GL lanes of a group, the result in every lane of it.
+template <int GL, typename T, typename F>
+__device__ inline T group_reduce(T v, F f) {
+    if (GL == 16) v = f(v, dpp_t<DPP_ROW_MIRROR>(v));
+    if (GL >= 8) v = f(v, dpp_t<DPP_HALF_MIRROR>(v));
+    v = f(v, dpp_t<DPP_SWAP2>(v));
+    return f(v, dpp_t<DPP_SWAP1>(v));
+}
+
+// The stepping rule in FP64 over the row (candidate positions from their own heads): the
+// lexicographic minimum of (D, place in the row) over the forward candidates; false if
+// there is none.
+template <int CTRL>
+__device__ inline void exact_stage(double& D, int& i, uint32_t& code) {
+    const double Do = dpp_d<CTRL>(D);
+    const int io = dpp_i<CTRL>(i);
+    const uint32_t co = (uint32_t)dpp_i<CTRL>((int)code);
+    const bool take = Do < D || (Do == D && io < i);
+    D = take ? Do : D;
+    i = take ? io : i;
+    code = take ? co : code;
 }
 
 template <int GL>
-__device__ inline int group_min_i(int v) {
-    if (GL == 16) v = dpp_min_i<DPP_ROW_MIRROR>(v);
-    if (GL >= 8) v = dpp_min_i<DPP_HALF_MIRROR>(v);
-    v = dpp_min_i<DPP_SWAP1>(v);
-    return dpp_min_i<DPP_SWAP2>(v);
+__device__ inline bool exact_step(const RowTab t, const char* row, int pieces, int sub, double ox, double oy, double oz,
+                                  double dx, double dy, double dz, double Zc, uint32_t& code) {
+    double D = __builtin_inf();
+    int best = INT32_MAX;
+    uint32_t c = 0;
+    for (int i = sub; i < pieces; i += GL) {
+        if (i < 2) continue;  // the head
+        const RowRec* rec = (const RowRec*)row + i;
+        if (rec->ex != rec->ex) continue;  // blank
+        const uint32_t ck = rec->code;
+        const RowHead* h = (const RowHead*)(t.recs + t.offset(ck));
+        const double Rx = h->x - ox, Ry = h->y - oy, Rz = h->z - oz;
+        const double Zk = __builtin_fma(Rz, dz, __builtin_fma(Ry, dy, Rx * dx));
+        if (!(Zk > Zc)) continue;
+        const double qx = __builtin_fma(-Zk, dx, Rx), qy = __builtin_fma(-Zk, dy, Ry), qz = __builtin_fma(-Zk, dz, Rz);
+        const double Dk = __builtin_fma(qz, qz, __builtin_fma(qy, qy, qx * qx));
+        if (Dk < D) {  // ascending places within the lane: the first of equal D stays
+            D = Dk;
+            best = i;
+            c = ck;
+        }
+    }
+    if (GL == 16) exact_stage<DPP_ROW_MIRROR>(D, best, c);
+    if (GL >= 8) exact_stage<DPP_HALF_MIRROR>(D, best, c);
+    exact_stage<DPP_SWAP2>(D, best, c);
+    exact_stage<DPP_SWAP1>(D, best, c);
+    code = c;
+    return best != INT32_MAX;
 }
 
 // Work order.  Without `order`, ray L is slot L (origin-major).  With `order`
@@ -214,21 +293,26 @@ __device__ inline int group_min_i(int v) {
 // their rays taken in order of length.  Blocks are renumbered so that each XCD
 // (own L2) takes runs of 16 consecutive blocks, the XCDs' runs side by side
 // (xcd_block, XCD_RUN_WALK).
-template <int MODE, int GL>
-__global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 4 : 1) void k_trace(const double* __restrict__ pos,
-                                                        const int2* __restrict__ rows,
-                                                        const NbrRec* __restrict__ nbr,
-                                                        const int32_t* __restrict__ nid, int64_t P,
-                                                        const int32_t* __restrict__ origins, int64_t n_origins,
-                                                        int64_t R, const double* __restrict__ dirs, int per_origin,
-                                                        int32_t* __restrict__ lens, const int64_t* __restrict__ ray_off,
-                                                        int32_t* __restrict__ ids, double* __restrict__ Zout,
-                                                        int64_t capacity, int32_t* __restrict__ err,
-                                                        const int32_t* __restrict__ order,
-                                                        const int32_t* __restrict__ ray_order, int n_xcd) {
+template <int MODE, int GL, bool FAR>
+__global__ __launch_bounds__(TRACE_BLOCK) void k_trace(
+    const double* __restrict__ pos, const RowTab t, int64_t P, const int32_t* __restrict__ origins, int64_t n_origins,
+    int64_t R, const double* __restrict__ dirs, int per_origin, int32_t* __restrict__ lens,
+    const int64_t* __restrict__ ray_off, int32_t* __restrict__ ids, double* __restrict__ Zout, int64_t capacity,
+    int32_t* __restrict__ err, const int32_t* __restrict__ order, const int32_t* __restrict__ ray_order, int n_xcd) {
     static_assert(GL == 4 || GL == 8 || GL == 16, "4, 8 or 16 lanes per ray");
-    constexpr int U = 32 / GL;  // candidates per lane per pass: a whole row of up to 32 in one round of loads
+    // 16-byte pieces of a row per lane per pass (4 lanes: 22 neighbours; 5 and 7 pieces 2% and
+    // 40% slower), and those of them that nearly every row has
+    constexpr int UW = GL == 4 ? 6 : 32 / GL, U0 = GL == 4 ? 3 : 1;
+    static_assert((UW - 1) * GL * 16 + 16 <= ROW_BLANK * 64, "blank records");
+    constexpr int RUNL = GL >= 8 ? GL : 8;                              // entries per stored block
+    constexpr int EPL = RUNL / GL;                                      // entries per lane per block
+    constexpr int RING = 2 * RUNL, RSTR = RING + 2;                     // the ring's entries, and its stride
+    constexpr int RAYS = TRACE_BLOCK / GL;
+    __shared__ __attribute__((aligned(16))) double ring_z[MODE == TRACE_COUNT ? 2 : RAYS * RSTR];
+    __shared__ __attribute__((aligned(16))) int32_t ring_i[MODE == TRACE_COUNT ? 2 : RAYS * RSTR];
     const int sub = threadIdx.x & (GL - 1);
+    double* const rz = ring_z + (MODE == TRACE_COUNT ? 0 : (threadIdx.x / GL) * RSTR);
+    int32_t* const ri = ring_i + (MODE == TRACE_COUNT ? 0 : (threadIdx.x / GL) * RSTR);
     const int64_t two_r = 2 * R;
     const int64_t n_rays = n_origins * two_r;
     const int64_t nb = (n_rays * GL + blockDim.x - 1) / blockDim.x;  // logical blocks
@@ -276,122 +360,146 @@ __global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 4 : 1) void k_trace(const do
         base = ray * capacity;  // capacity = slots per ray
         room = (int32_t)capacity;
     }
-    const int2 row0 = rows[o];
-    int32_t e0 = row0.x, deg = row0.y;
-    int32_t n = 0;
-    double Zc = 0.0;
-    constexpr int RUNL = GL >= 8 ? GL : 8;  // entries per stored block
-    constexpr int EPL = RUNL / GL;          // entries per lane per block
-    int32_t ke[2 * EPL];                    // the ring: [block][entry] as record indices
-    double kz[2 * EPL];
-#pragma unroll
-    for (int i = 0; i < 2 * EPL; ++i) {
-        ke[i] = 0;
-        kz[i] = 0.0;
-    }
-    // end of the last stored block (blocks before the one holding `base` count as stored)
-    int64_t p_last = (base & ~(int64_t)(RUNL - 1)) - 1;
-    // the group's EPL entries of the block starting at S (ring half rb), positions below
-    // `lo` and from `hi` on left out
-    auto store_block = [&](int64_t S, int rb, int64_t lo, int64_t hi) {
+    const float fx = (float)dx, fy = (float)dy, fz = (float)dz;
+    uint32_t code = t.code[o];
+    int32_t n = 0;                                 // list entries so far
+    int32_t slot = (int32_t)(base - 1) & (RING - 1);  // the current point's place in the ring
+    // the group's entries of the block starting at position S; positions outside the list
+    // (before base, from hi on) are left out
+    auto store_block = [&](int64_t S, int64_t hi) {
         const int64_t q = S + sub * EPL;
-        if (EPL == 2 && q >= lo && q + 1 < hi) {
-            *(int2*)(ids + q) = make_int2(nid[ke[2 * rb]], nid[ke[2 * rb + 1]]);
-            *(double2*)(Zout + q) = make_double2(kz[2 * rb], kz[2 * rb + 1]);
+        const int k = (int)q & (RING - 1);
+        if (EPL > 1 && q >= base && q + EPL <= hi) {
+            *(int2*)(ids + q) = *(const int2*)(ri + k);
+            *(double2*)(Zout + q) = *(const double2*)(rz + k);
         } else {
 #pragma unroll
             for (int e = 0; e < EPL; ++e)
-                if (q + e >= lo && q + e < hi) {
-                    ids[q + e] = nid[ke[rb * EPL + e]];
-                    Zout[q + e] = kz[rb * EPL + e];
+                if (q + e >= base && q + e < hi) {
+                    ids[q + e] = ri[k + e];
+                    Zout[q + e] = rz[k + e];
                 }
         }
     };
-    for (int32_t step = 0; step < (int32_t)P; ++step) {
-        Cand b;
-        b.D = __builtin_inf();
-        b.Z = 0.0;
-        b.e = INT32_MAX;
-        b.start = 0;
-        b.deg = 0;
-        // GL lanes x U candidates per pass (32 entries); a lane's U loads are issued together
-        for (int32_t i0 = 0; i0 < deg; i0 += U * GL) {
-            NbrRec rec[U];
+    for (int32_t count = 0;; ++count) {
+        const int32_t step = __builtin_amdgcn_readfirstlane(count);  // the same in every active lane
+        // the row, UW pieces of 16 bytes a lane (past the row's end: blank records); the first
+        // two pieces are the head
+        const char* row = t.recs + (FAR ? t.offset(code) : (uint64_t)(uint32_t)t.offset(code));
+        int pieces = 4 * t.units(code);
+        if (__builtin_amdgcn_ballot_w64(t.more(code)))
+            if (t.more(code)) pieces = (int)((((const RowRec*)row)[2].code + 6) / 4 * 4);
+        const int lim = pieces - sub;
+        const uint64_t at0 = (FAR ? t.offset(code) : (uint64_t)(uint32_t)t.offset(code)) + (uint32_t)sub * 16;
+        f32x4 rec[UW];
+        bool any[UW];
 #pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t i = i0 + u * GL + sub;
-                if (i < deg) rec[u] = nbr[e0 + i];
-            }
-#pragma unroll
-            for (int u = 0; u < U; ++u) {
-                const int32_t i = i0 + u * GL + sub;
-                if (i >= deg) continue;
-                const double Rx = rec[u].x - ox, Ry = rec[u].y - oy, Rz = rec[u].z - oz;
-                const double Zk = __builtin_fma(Rz, dz, __builtin_fma(Ry, dy, Rx * dx));
-                if (!(Zk > Zc)) continue;
-                const double qx = __builtin_fma(-Zk, dx, Rx), qy = __builtin_fma(-Zk, dy, Ry),
-                             qz = __builtin_fma(-Zk, dz, Rz);
-                const double Dk = __builtin_fma(qz, qz, __builtin_fma(qy, qy, qx * qx));
-                if (Dk < b.D) {  // ascending ids within the lane: the first of equal D has the smaller id
-                    b.D = Dk;
-                    b.Z = Zk;
-                    b.e = (int32_t)(e0 + i);
-                    b.start = rec[u].start;
-                    b.deg = rec[u].deg;
-                }
+        for (int i = 0; i < UW; ++i) {
+            const bool has = (GL == 4 && i == 0) || i * GL < lim;  // every row has four pieces
+            any[i] = i < U0 || __builtin_amdgcn_ballot_w64(has);
+            if (any[i]) {
+                const uint64_t at = has ? at0 : 0;
+                rec[i] = *(const f32x4*)(t.recs + (FAR ? at : (uint64_t)(uint32_t)at) + i * GL * 16);
             }
         }
-        // group minimum of (D, record index); within the sorted row the smaller
-        // index is the smaller id, so this is the minimum of (D, id)
-        const double Dmin = group_min_d<GL>(b.D);
-        const int32_t emin = group_min_i<GL>(b.D == Dmin ? b.e : INT32_MAX);
-        if (emin == INT32_MAX) break;  // no forward neighbour: the ray leaves the model
-        // the winner's Z and row, read from the lane that holds it
-        const uint64_t won = __ballot(b.D == Dmin && b.e == emin);
-        const int gbase = (int)(threadIdx.x & 63) & ~(GL - 1);
-        const uint32_t gbits = (uint32_t)(won >> gbase) & (uint32_t)((1ull << GL) - 1);
-        const int src = gbase + __builtin_ctz(gbits);
-        const double Zn = bperm_d(src, b.Z);
-        const int32_t start_n = bperm_i(src, b.start);
-        const int32_t deg_n = bperm_i(src, b.deg);
-        if (MODE != TRACE_COUNT) {
-            if (n >= room) {
-                if (sub == 0) atomicOr(err, ERRBIT_CAPACITY);
-                break;
-            }
-            const int64_t at = base + n;  // absolute list position of this entry
-            const int o = (int)(at & (RUNL - 1));
-            if (sub == o / EPL) {
-                const int k = (int)((at / RUNL) & 1) * EPL + o % EPL;
+        // the head, from the group's first two lanes (one quad each) or loaded again
+        const u32x4 w0 = __builtin_bit_cast(u32x4, rec[0]);
+        u32x4 hxy, hzi;
+        if (GL == 4) {
 #pragma unroll
-                for (int i = 0; i < 2 * EPL; ++i)
-                    if (i == k) {
-                        ke[i] = emin;
-                        kz[i] = Zn;
-                    }
+            for (int k = 0; k < 4; ++k) {
+                hxy[k] = (uint32_t)dpp_i<DPP_LANE0>((int)w0[k]);
+                hzi[k] = (uint32_t)dpp_i<DPP_LANE1>((int)w0[k]);
             }
-            if ((n & (RUNL - 1)) == RUNL - 1) {  // the step of the wave's stores
-                const int64_t Pend = at - ((at + 1) & (RUNL - 1));  // end of the last completed block
-                const int64_t S = Pend - (RUNL - 1);
-                store_block(S, (int)((S / RUNL) & 1), base, at + 1);
-                p_last = Pend;
+        } else {
+            hxy = *(const u32x4*)row;
+            hzi = *(const u32x4*)(row + 16);
+        }
+        if (sub < 2) rec[0].x = NAN;
+        // the current point: its exact projection and offset from the axis
+        const double Rx = make_f64(hxy[0], hxy[1]) - ox, Ry = make_f64(hxy[2], hxy[3]) - oy,
+                     Rz = make_f64(hzi[0], hzi[1]) - oz;
+        const double Z = __builtin_fma(Rz, dz, __builtin_fma(Ry, dy, Rx * dx));
+        n = step;
+        if (MODE != TRACE_COUNT) {  // record it (the origin's place, before the list, is never stored)
+            if (sub == 0) {
+                ri[slot] = (int32_t)hzi[2];
+                rz[slot] = Z;
+            }
+            slot = (slot + 1) & (RING - 1);
+            if (step > 0 && (step & (RUNL - 1)) == 0) {  // the step of the wave's stores: the last block completed
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
+                const int64_t end = base + step;
+                store_block((end & ~(int64_t)(RUNL - 1)) - RUNL, end < base + room ? end : base + room);
+                __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+                __builtin_amdgcn_wave_barrier();
             }
         }
-        ++n;
-        e0 = start_n;
-        deg = deg_n;
-        Zc = Zn;
+        if (step >= (int32_t)P) break;  // Z grows at every step, so no ray is longer
+        double qx = __builtin_fma(-Z, dx, Rx), qy = __builtin_fma(-Z, dy, Ry), qz = __builtin_fma(-Z, dz, Rz), Zs = Z;
+        if (t.scale != 1.0) {
+            qx *= t.scale;
+            qy *= t.scale;
+            qz *= t.scale;
+            Zs *= t.scale;
+        }
+        const float px = (float)qx, py = (float)qy, pz = (float)qz;
+        const float E = __builtin_bit_cast(float, (uint32_t)hzi[3]);
+        const float P1 = fabsf(px) + fabsf(py) + fabsf(pz);
+        const float Rm = fabsf((float)Zs) + P1, A = __builtin_fmaf(Rm, 0x1p-40f, P1 + E);
+        const float tol_s = __builtin_fmaf(A, 0x1p-21f, __builtin_fmaf(Rm, 0x1p-48f, t.floor_s));
+        const float tol_D = __builtin_fmaf(10.f * A, tol_s, t.floor_D);
+        const float inf = __builtin_inff();
+        float D1 = inf, D2 = inf;  // the lane's two least D, and the first's row code
+        uint32_t best = 0;
+        bool unsure = false;
+        auto weigh = [&](const f32x4 q) {
+            const float tx = px + q.x, ty = py + q.y, tz = pz + q.z;
+            const float s = __builtin_fmaf(q.z, fz, __builtin_fmaf(q.y, fy, q.x * fx));
+            const float T = __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx));
+            const float D = s > tol_s ? __builtin_fmaf(-s, s, T) : inf;
+            unsure = unsure || fabsf(s) <= tol_s;
+            D2 = __builtin_amdgcn_fmed3f(D1, D2, D);
+            const bool first = D < D1;
+            D1 = first ? D : D1;
+            best = first ? __builtin_bit_cast(uint32_t, (float)q.w) : best;
+        };
+#pragma unroll
+        for (int i = 0; i < UW; ++i)
+            if (any[i]) weigh(rec[i]);
+        if (__builtin_amdgcn_ballot_w64(UW * GL < lim))
+            for (int i = UW * GL; i < lim; i += GL)  // rows longer than one pass
+                weigh(*(const f32x4*)(row + (int64_t)(sub + i) * 16));
+        D2 = unsure ? -inf : D2;
+        const float least = group_reduce<GL>(D1, [](float a, float o) { return o < a ? o : a; });
+        const float lim_D = least + tol_D;
+        // candidates that may be the rule's choice: one means it is known
+        const bool mine = D1 <= lim_D;
+        const int rivals = group_reduce<GL>((mine ? 1 : 0) + (D2 <= lim_D ? 2 : 0), [](int a, int o) { return a + o; });
+        code = group_reduce<GL>(mine ? best : 0u, [](uint32_t a, uint32_t o) { return a > o ? a : o; });
+        if (rivals != 1) {
+            // none forward (D1 = D2 = inf in every lane): the ray leaves the model
+            if (least == inf && group_reduce<GL>(D2, [](float a, float o) { return o < a ? o : a; }) == inf) break;
+            if (!exact_step<GL>(t, row, pieces, sub, ox, oy, oz, dx, dy, dz, Z, code)) break;
+        }
     }
-    if (MODE != TRACE_COUNT) {  // what is left: at most the two ring blocks after p_last
-#pragma unroll
-        for (int b2 = 0; b2 < 2; ++b2) {
-            const int64_t S = p_last + 1 + (int64_t)b2 * RUNL;
-            if (S < base + n) store_block(S, (int)((S / RUNL) & 1), base, base + n);
-        }
+    if (MODE != TRACE_COUNT) {
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
+        // a ray longer than its slot is cut there; one shorter than its slot leaves entries
+        // unwritten: the offsets do not match this walk
+        if (sub == 0 && (n > room || (MODE == TRACE_WRITE && n < room))) atomicOr(err, ERRBIT_CAPACITY);
+        // what is left: at most the two ring blocks after the last stored one
+        const int64_t done = base + (n & ~(RUNL - 1));  // the list's end at the last stores
+        int64_t S = n >= RUNL ? (done & ~(int64_t)(RUNL - 1)) : (base & ~(int64_t)(RUNL - 1));
+        if (n > room) n = room;
+        for (int k = 0; k < 2; ++k, S += RUNL)
+            if (S < base + n) store_block(S, base + n);
+        __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+        __builtin_amdgcn_wave_barrier();
     }
     if (MODE != TRACE_WRITE && sub == 0) lens[ray] = n;
-    // a ray shorter than its slot leaves entries unwritten: the offsets do not match this walk
-    if (MODE == TRACE_WRITE && sub == 0 && n < room) atomicOr(err, ERRBIT_CAPACITY);
     }
 }
 
@@ -500,31 +608,44 @@ inline int64_t blocks_for(int64_t n, int b) { return (n + b - 1) / b; }
 
 }  // namespace
 
-hipError_t launch_check_model(const rt_model* m, int32_t* bad, hipStream_t s) {
+hipError_t launch_check_model(const rt_model* m, int32_t* bad, uint64_t* reach, hipStream_t s) {
     hipLaunchKernelGGL(k_check_off, dim3((unsigned)blocks_for(m->P, 256)), dim3(256), 0, s, m->off, m->idx, m->pos, m->P,
-                       m->E, bad);
+                       m->E, bad, (unsigned long long*)reach);
     return hipGetLastError();
 }
 
 static size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 
-size_t build_nbr_workspace(int64_t P) {
+// Row addresses are 32-bit codes: the start in units of 64 << sh bytes above nb bits for the
+// number of units.  28 bits of start and units of 64 bytes reach 17 GB of rows, far beyond
+// any model measured; larger models give up the four bits (every row holds its degree) and
+// take units of 128 bytes, which reach every model the ABI accepts.
+size_t plan_rows(RowTab& t, int64_t P, int64_t E) {
+    const int64_t units = ROW_BLANK + 2 * P + E / 4;  // of 64 bytes, at most
+    const bool wide = units >= (int64_t)1 << 28;
+    t.nb = wide ? 0 : 4;
+    t.sh = wide ? 1 : 0;
+    return (size_t)(units + (wide ? P : 0)) * 64;
+}
+
+size_t build_rows_workspace(int64_t P) {
     return al256(sizeof(int32_t) * (size_t)P) + al256(sizeof(int64_t) * (size_t)(P + 1)) + al256(scan_workspace(P));
 }
 
-hipError_t launch_build_nbr(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s) {
-    int32_t* deg = (int32_t*)ws;
+hipError_t launch_build_rows(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s) {
+    int32_t* units = (int32_t*)ws;
     int64_t* start = (int64_t*)((char*)ws + al256(sizeof(int32_t) * (size_t)m->P));
     void* scan_ws = (char*)start + al256(sizeof(int64_t) * (size_t)(m->P + 1));
     const unsigned g = (unsigned)blocks_for(m->P, 256);
-    hipLaunchKernelGGL(k_layout_deg, dim3(g), dim3(256), 0, s, m->off, lay, m->P, deg);
-    hipError_t e = launch_scan(deg, m->P, start, scan_ws, s);
+    hipLaunchKernelGGL(k_layout_units, dim3(g), dim3(256), 0, s, m->off, lay, m->P, m->tab.sh, m->tab.nb,
+                       units);
+    hipError_t e = launch_scan(units, m->P, start, scan_ws, s);
     if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_layout_rows, dim3(g), dim3(256), 0, s, start, deg, lay, m->P, m->rows);
-    if (m->E > 0) {
-        hipLaunchKernelGGL(k_build_nbr, dim3(g), dim3(256), 0, s, m->pos, m->P, m->off, m->idx, m->rows, m->nbr, m->nid);
-        hipLaunchKernelGGL(k_sort_rows, dim3(g), dim3(256), 0, s, m->rows, m->P, m->nbr, m->nid, key);
-    }
+    hipLaunchKernelGGL(k_layout_codes, dim3(g), dim3(256), 0, s, start, m->off, lay, m->P, m->tab.nb,
+                       (int64_t)(ROW_BLANK >> m->tab.sh), m->codes);
+    hipLaunchKernelGGL(k_blank_rows, dim3(1), dim3(ROW_BLANK * 4), 0, s, (RowRec*)m->recs, ROW_BLANK * 4);
+    hipLaunchKernelGGL(k_build_rows, dim3((unsigned)blocks_for(m->P * BUILD_LANES, 256)), dim3(256), 0, s, m->pos, m->P,
+                       m->off, m->idx, key, m->tab, m->recs);
     return hipGetLastError();
 }
 
@@ -536,19 +657,18 @@ static hipError_t trace_launch(const rt_model* m, const int32_t* origins, int64_
     const int64_t n = n_origins * 2 * R;
     if (n == 0) return hipSuccess;
     if (gl != 8 && gl != 16) gl = 4;  // 0 and other values: the default, 4 lanes
+    const bool far = m->row_bytes > 0xFFFFFFFFull;  // rows beyond 32-bit offsets: 4 lanes
+    if (far) gl = 4;
     int32_t* ew = MODE == TRACE_COUNT ? nullptr : error_word();
-    if (gl == 16)
-        hipLaunchKernelGGL((k_trace<MODE, 16>), dim3(capped_blocks(blocks_for(n * 16, TRACE_BLOCK))), dim3(TRACE_BLOCK), 0, s, m->pos,
-                           m->rows, m->nbr, m->nid, m->P, origins, n_origins, R, dirs, per_origin, lens, ray_off, ids, Z,
-                           capacity, ew, order, ray_order, num_xcds());
-    else if (gl == 8)
-        hipLaunchKernelGGL((k_trace<MODE, 8>), dim3(capped_blocks(blocks_for(n * 8, TRACE_BLOCK))), dim3(TRACE_BLOCK), 0, s, m->pos,
-                           m->rows, m->nbr, m->nid, m->P, origins, n_origins, R, dirs, per_origin, lens, ray_off, ids, Z,
-                           capacity, ew, order, ray_order, num_xcds());
-    else
-        hipLaunchKernelGGL((k_trace<MODE, 4>), dim3(capped_blocks(blocks_for(n * 4, TRACE_BLOCK))), dim3(TRACE_BLOCK), 0, s, m->pos,
-                           m->rows, m->nbr, m->nid, m->P, origins, n_origins, R, dirs, per_origin, lens, ray_off, ids, Z,
-                           capacity, ew, order, ray_order, num_xcds());
+    const dim3 grid(capped_blocks(blocks_for(n * gl, TRACE_BLOCK)));
+#define RT_TRACE(GL_, FAR_)                                                                                      \
+    hipLaunchKernelGGL((k_trace<MODE, GL_, FAR_>), grid, dim3(TRACE_BLOCK), 0, s, m->pos, m->tab, m->P, origins, \
+                       n_origins, R, dirs, per_origin, lens, ray_off, ids, Z, capacity, ew, order, ray_order, num_xcds())
+    if (far) RT_TRACE(4, true);
+    else if (gl == 16) RT_TRACE(16, false);
+    else if (gl == 8) RT_TRACE(8, false);
+    else RT_TRACE(4, false);
+#undef RT_TRACE
     return hipGetLastError();
 }
 
