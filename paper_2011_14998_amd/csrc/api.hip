@@ -611,6 +611,7 @@ rt_status rt::fill_solve_launch(const rt_model* m, rt_dirset* set, const int32_t
     }
     a.err = error_word();
     if (!a.err) return fail(RT_ERR_HIP, "solve: no device error word");
+    plan_lines(a, o.precision);
     return RT_OK;
 }
 
@@ -797,6 +798,7 @@ struct rt_plan {
     std::vector<OrderSeg> segs;
     // the solve launch as filled from the caller's arguments, before any schedule is applied
     SolveLaunch base;
+    void* pad = nullptr;       // padded tables of the multi-line sweep (moving media), refilled by every run
     void* u_buf = nullptr;
     void* bin_buf = nullptr;   // binned schedule: queue counter + bins, allocated on first use
     hipStream_t stream = nullptr;
@@ -850,6 +852,7 @@ static hipError_t plan_enqueue(rt_plan* p, hipStream_t s, hipEvent_t* ev = nullp
         e = launch_fill_i32(a.queue, 1, 0, s);
     }
     mark(4);
+    if (e == hipSuccess && a.pad_chi) e = launch_pad(a, p->o.precision, s);
     if (e == hipSuccess) e = launch_solve(a, p->o.precision, s);
     mark(5);
     if (e == hipSuccess) e = launch_reduce(a, p->o.precision, s);
@@ -864,7 +867,7 @@ static void plan_free(rt_plan* p) {
     if (p->exec) (void)hipGraphExecDestroy(p->exec);
     if (p->graph) (void)hipGraphDestroy(p->graph);
     for (void* q : {(void*)p->lens, (void*)p->ray_off, p->scan_ws, p->solve_ws, (void*)p->order, p->bin_buf,
-                    (void*)p->pair_order, (void*)p->walk_order})
+                    (void*)p->pair_order, (void*)p->walk_order, p->pad})
         if (q) (void)hipFree(q);
     const int dev = p->m->device;
     pool_free(p->ids, p->ids_bytes, dev);
@@ -1225,6 +1228,19 @@ rt_status rt::plan_create_ordered(const rt_model* m, rt_dirset* set, const int32
     if (st) {
         plan_free(p);
         return st;
+    }
+    // Moving media: the multi-line sweep reads padded copies of the tables, remade by every run.  A row's
+    // copy costs about what the sweep of 16 of its line points saves, so models that the lists visit
+    // less than 32 times per point keep the caller's tables (and so they do without memory for copies).
+    if (p->a.vpl && p->a.vel && p->total >= 32 * m->P) {
+        const size_t pb = align_up(pad_table_bytes(p->a, p->o.precision));
+        if (hipMalloc(&p->pad, 2 * pb) == hipSuccess) {
+            p->a.pad_chi = p->pad;
+            p->a.pad_eta = (char*)p->pad + pb;
+        } else {
+            (void)hipGetLastError();
+            p->pad = nullptr;
+        }
     }
     p->base = p->a;
     const size_t es = p->o.precision == RT_F64 ? 8 : 4;

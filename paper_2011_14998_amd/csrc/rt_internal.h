@@ -46,10 +46,12 @@ inline unsigned capped_blocks(int64_t n_blocks) {
 // contiguous range per XCD made the walk of the 64-cloud batch 14% slower).  A
 // bijection of [0, G) for any grid size G: the blocks past the last whole
 // group of n runs keep their own number.  Run lengths: the walk 16 workgroups
-// (16 windows of 64 origins), the sweep 256 (1024 items); measured on the batch
-// and the octree.
+// (16 windows of 64 origins), the sweep 256 (1024 items), the multi-line sweep
+// 64 (256 waves: as many lines; 16 measured the same); measured on the batch and
+// the octree.
 constexpr int64_t XCD_RUN_WALK = 16;
 constexpr int64_t XCD_RUN_SWEEP = 256;
+constexpr int64_t XCD_RUN_LINES = 64;
 __device__ inline int64_t xcd_block(int64_t b, int64_t G, int n, int64_t R) {
     if (n <= 1) return b;
     const int64_t span = (int64_t)n * R, full = G / span * span;
@@ -220,7 +222,16 @@ struct SolveLaunch {
     int group;             // sweep load-group size (4 or 8)
     int small_tables;      // chi and eta each below 4 GiB: 32-bit row offsets in the sweep
     int scheme;            // RT_SCHEME_FEAUTRIER2 or RT_SCHEME_HERMITE
+    // several lines per wave (plan_lines): frequencies per lane (0: not applicable), lanes per line, lines
+    // per wave, chunks of 64 lanes per line; moving media: padded tables (nullptr: none) and their row length
+    int vpl, lpl, lines, line_chunks;
+    int pad_ld;
+    void* pad_chi;
+    void* pad_eta;
 };
+bool plan_lines(SolveLaunch& a, int precision);
+size_t pad_table_bytes(const SolveLaunch& a, int precision);
+hipError_t launch_pad(const SolveLaunch& a, int precision, hipStream_t s);
 int64_t solve_items(const SolveLaunch& a);
 // Items a persistent wave takes per queue atomic, the cap on its grid (waves per
 // CU), and so the largest item count whose int32 queue counter cannot overflow.

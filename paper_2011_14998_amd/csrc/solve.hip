@@ -30,8 +30,16 @@
 // of positive numbers, so small optical-depth steps lose nothing to
 // cancellation.  At the origin (a, b the steps to the two sides' last rows)
 //     u = ((a+b)/2 S + Y_- + Y_+) / ((a+b)/2 + G_- r_- + G_+ r_+),
-// and with one side empty (dtau t on the other)
-//     u = (t/2 S + I + Y) / (1 + t/2 + G r).
+// and a side without points counts as a = 0, G = r = 1, Y = I.
+//
+// As computed (Row2): steps are carried divided by sqrt 2 and G and Y times
+// sqrt 2, which leaves every formula above as it is but for (a+b)/2, now a + b,
+// and G = r = 1, Y = I before the far end, now G = sqrt 2, Y = sqrt 2 I.  With S_d
+// = e/c the row's two quotients share the reciprocal q = 1/(D c), D = 1 + b G:
+//     r = q c,  Y = (h e + c Y_{d-1}) q,  h = a + b:
+// ten operations and one reciprocal.  A line starts from that state with c = 1,
+// e = 0 and no step, for which the row changes nothing, exactly; so every point
+// takes the same row, the first included.
 //
 // Per-point data that is the same for every frequency (point id, ds, the
 // velocity projection) is loaded for 64 points at once, one per lane, and
@@ -152,55 +160,57 @@ __device__ inline float rcp<float>(float x) { return __builtin_amdgcn_rcpf(x); }
 template <>
 __device__ inline double rcp<double>(double x) { return rcp64(x); }
 
-// Running state of one side's elimination (file header).
+// The second-order elimination (file header): steps are ds times HALF_STEP times the sum of
+// the end points' opacities.
+constexpr double SQRT2 = 1.4142135623730951;
+constexpr double HALF_STEP2 = 0.35355339059327379;  // 1/2 / sqrt 2
+
 template <typename T>
-struct SweepState {
-    T G, Y, r;  // rescaled pivot and right-hand side, r = 1/(1 + a G)
-    T a;        // inner optical-depth step of the last row: the outer step of the next
-    // fourth-order rows: u_d = (1 - F) u_{d+1} + Z; S (FP64) of the last row's
-    // point and of its next point; whether a row met a step beyond the limit
-    T F, Z;
-    double Sp, Sc;
-    bool bad;
+struct Row2 {
+    T G, Y, r;  // rescaled pivot and right-hand side, r = 1/(1 + b G)
+    T a;        // inner step of the last row: the outer step of the next
 };
 
-// Row d of the elimination, given its inner step b and S_d (the outer step is st.a).
 template <typename T>
-__device__ inline void row(SweepState<T>& st, bool far_end, T b, T S, T I) {
-    if (far_end) {
-        const T hb = (T)0.5 * b;
-        st.G = (T)1 + hb;
-        st.r = rcp<T>(fma_<T>(b, st.G, (T)1));
-        st.Y = fma_<T>(hb, S, I) * st.r;
-    } else {
-        const T h = (T)0.5 * (st.a + b);
-        st.G = fma_<T>(st.G, st.r, h);
-        st.r = rcp<T>(fma_<T>(b, st.G, (T)1));
-        st.Y = fma_<T>(h, S, st.Y) * st.r;
-    }
-    st.a = b;
+__device__ inline void row2_start(Row2<T>& st, T I) {
+    st.G = (T)SQRT2;
+    st.r = (T)1;
+    st.a = (T)0;
+    st.Y = (T)SQRT2 * I;
 }
 
-// Row d of the second-order elimination for a point of opacity c whose source the
-// next row needs: the row's reciprocal r = 1/D (D = 1 + b G) and 1/c come from one
-// reciprocal of their product, q = 1/(D c), r = q c, 1/c = q D (three multiplies
-// instead of a second quarter-rate reciprocal; D >= 1 and c > 0, so the product
-// neither cancels nor, for opacities below ~1e30, overflows).  Returns 1/c.  The sweep
-// starts a side from the state G = 1, r = 1, a = 0, Y = I, on which this generic row
-// with the far end's step is the far-end row of `row` (G = 1 + b/2, Y = (b/2 S + I) r),
-// and runs it for the first point too, with b = 0: that row leaves G = 1, a = 0 and
-// r, Y within an ulp of 1 and I, and yields the first point's 1/c.
+// The row of the point with opacity c and emissivity e, given its inner step b.  (D >= 1 and c > 0, so
+// D c neither cancels nor, for opacities below ~1e30, overflows.)
 template <typename T>
-__device__ inline T row_rc(SweepState<T>& st, T b, T S, T c) {
-    const T h = (T)0.5 * (st.a + b);
+__device__ inline void row2(Row2<T>& st, T b, T c, T e) {
+    const T h = st.a + b;
     st.G = fma_<T>(st.G, st.r, h);
     const T D = fma_<T>(b, st.G, (T)1);
     const T q = rcp<T>(D * c);
     st.r = q * c;
-    st.Y = fma_<T>(h, S, st.Y) * st.r;
+    st.Y = fma_<T>(h, e, c * st.Y) * q;
     st.a = b;
-    return q * D;
 }
+
+// u at the origin from the two sides' states (file header); I when both sides are empty.
+template <typename T>
+__device__ inline T origin_u(bool any, T ma, T mGr, T mY, T pa, T pGr, T pY, T S, T I) {
+    const T h = ma + pa;
+    const T u = fma_<T>(h, S, mY + pY) * rcp<T>(h + (mGr + pGr));
+    return any ? u : I;
+}
+
+// Running state of one side's elimination: rows of the chosen scheme.
+template <typename T>
+struct SweepState {
+    Row2<T> s;  // second-order rows
+    // fourth-order rows: u_d = (1 - F) u_{d+1} + Z; the last row's inner step; S (FP64) of the
+    // last row's point and of its next point; whether a row met a step beyond the limit
+    T F, Z;
+    T a;
+    double Sp, Sc;
+    bool bad;
+};
 
 // Fourth-order (Hermitian) rows with third-order end rows: the scheme Section
 // 2.1 names for the solver (Auer 1976); derived from exactness for quartic u.
@@ -303,28 +313,18 @@ __device__ inline T origin_h(bool hm, bool hp, SweepState<T>& m, SweepState<T>& 
     return I;
 }
 
-// A row of the chosen scheme.  SCH 0, second order: the point's S.  SCH 1,
-// fourth order: the point's optics and the next point's (cn, en).
+// A row of the chosen scheme, given the point's optics (c, e) and the next point's (cn, en, which
+// only the fourth-order rows read).
 template <typename T, int SCH>
-__device__ inline void row_s(SweepState<T>& st, bool far_end, T b, T S, T c, T e, T cn, T en, T I) {
+__device__ inline void row_s(SweepState<T>& st, bool far_end, T b, T c, T e, T cn, T en, T I) {
     if (SCH == 1) row_h<T>(st, far_end, b, c, e, cn, en, I);
-    else row<T>(st, far_end, b, S, I);
+    else row2<T>(st.s, b, c, e);
 }
 
-// u at the origin from the two sides' states (file header).
-template <typename T>
-__device__ inline T origin_u(bool hm, bool hp, const SweepState<T>& m, const SweepState<T>& p, T S, T I) {
-    if (hm && hp) {
-        const T h = (T)0.5 * (m.a + p.a);
-        return fma_<T>(h, S, m.Y + p.Y) * rcp<T>(h + fma_<T>(m.G, m.r, p.G * p.r));
-    }
-    if (hm || hp) {
-        const SweepState<T>& q = hp ? p : m;
-        const T ht = (T)0.5 * q.a;
-        return (fma_<T>(ht, S, I) + q.Y) * rcp<T>(fma_<T>(q.G, q.r, (T)1 + ht));
-    }
-    return I;
-}
+// What the sum of two end points' opacities is multiplied by, over the interval's length, to give the
+// step as the scheme's rows carry it.
+template <int SCH>
+constexpr double half_step() { return SCH == 0 ? HALF_STEP2 : 0.5; }
 
 // Per-wave constants of one item.
 struct ItemCtx {
@@ -372,86 +372,65 @@ __device__ inline double chi64(const Pt64<T>& p) {
 
 // Interval from the far point (chi cf, eta ef, S Sf) to the near point (cn, en)
 // of one side: n = ceil(max(chi'_far, chi'_near) ds / dtau_max), clamped to
-// 1 .. max_sub; hds is half the interval's length.  When the kernel-precision
+// 1 .. max_sub; hds is the interval's length times half_step.  When the kernel-precision
 // estimate is below 1 - 1e-4 in every lane (it is within a few ulps of the FP64
 // value) n is 1 everywhere and the FP64 evaluation is skipped.  The n-1
 // interior points interpolate chi' and eta' linearly; rows are emitted far to
 // near, each with its inner step, the last being the sub-point next to the near
 // point.  `first` marks the far end of the line (its row is the boundary row).
-// With the second-order rows (SCH 0) every row whose near point is a line point forms that
-// point's 1/chi with the row's reciprocal (row_rc) and the interval returns it; the row into
-// the origin (to_origin) is the plain row, a far-end row when it is the line's first.
 template <typename T, int SCH>
-__device__ inline T near_row(SweepState<T>& st, bool first, T b, T Sf, T cf, T ef, T cn, T en, T I, bool to_origin) {
-    if (SCH == 0) {
-        if (!to_origin) return row_rc<T>(st, b, Sf, cn);
-        row<T>(st, first, b, Sf, I);
-        return (T)0;
+__device__ inline void substep_interval(const ItemCtx& c, SweepState<T>& st, bool first, T cf, T ef, T cn, T en, T hds,
+                                        const Pt64<T>& pf, const Pt64<T>& pn, double ds64, T I) {
+    const T est = (cf > cn ? cf : cn) * (T)ds64 * (T)c.dtau_rcp;
+    if (!__builtin_amdgcn_ballot_w64(est > (T)0.9999)) {
+        row_s<T, SCH>(st, first, (cf + cn) * hds, cf, ef, cn, en, I);
+        return;
     }
-    row_s<T, SCH>(st, first, b, Sf, cf, ef, cn, en, I);
-    return (T)0;
-}
-
-template <typename T, int SCH>
-__device__ inline T substep_interval(const ItemCtx& c, SweepState<T>& st, bool first, T cf, T ef, T Sf, T cn, T en,
-                                     T hds, const Pt64<T>& pf, const Pt64<T>& pn, double ds64, T I, bool to_origin) {
-    const T est = (cf > cn ? cf : cn) * (hds + hds) * (T)c.dtau_rcp;
-    if (!__builtin_amdgcn_ballot_w64(est > (T)0.9999))
-        return near_row<T, SCH>(st, first, (cf + cn) * hds, Sf, cf, ef, cn, en, I, to_origin);
     const double c64f = chi64(pf), c64n = chi64(pn);
     const double cm = c64f > c64n ? c64f : c64n;
     double q = ceil((cm * ds64) * c.dtau_rcp);
     if (q > (double)c.max_sub) q = (double)c.max_sub;
     const int n = q >= 1.0 ? (int)q : 1;  // also 1 for a NaN
     const T rn = rcp<T>((T)n);
-    const T hh = hds * rn;  // half a sub-interval
-    T cp = cf, ep = ef, Sp = Sf;
+    const T hh = hds * rn;  // hds of a sub-interval
+    T cp = cf, ep = ef;
     bool fr = first;
     for (int k = 1; __builtin_amdgcn_ballot_w64(k < n); ++k) {
         if (k < n) {
             const T w = (T)k * rn;
             const T ck = fma_<T>(w, cn - cf, cf);
             const T ek = fma_<T>(w, en - ef, ef);
-            const T ic = near_row<T, SCH>(st, fr, (cp + ck) * hh, Sp, cp, ep, ck, ek, I, false);
+            row_s<T, SCH>(st, fr, (cp + ck) * hh, cp, ep, ck, ek, I);
             cp = ck;
             ep = ek;
-            if (SCH == 0) Sp = ek * ic;
             fr = false;
         }
     }
-    return near_row<T, SCH>(st, fr, (cp + cn) * hh, Sp, cp, ep, cn, en, I, to_origin);
+    row_s<T, SCH>(st, fr, (cp + cn) * hh, cp, ep, cn, en, I);
 }
 
 // The stream of line points of one side, far to near, after velocity sampling.
 template <typename T>
 struct Emitter {
-    T c, e, S;
+    T c, e;
     Pt64<T> p;
     bool first = true;  // no row emitted yet: the next one is the boundary row
     bool have = false;
 };
 
-// Emit the next line point; the interval from the previous one (half length
-// hds, FP64 length ds64) is split by optical depth when that is on.
-// (SCH 0: Sn is ignored and formed from the row's reciprocal, the first point's from the
-// harmless row of row_rc; the state starts as row_rc describes.)
+// Emit the next line point; the interval from the previous one (hds: its length times
+// half_step, FP64 length ds64) is split by optical depth when that is on.
 template <typename T, int SCH>
-__device__ inline void emit_point(const ItemCtx& c, SweepState<T>& st, Emitter<T>& em, T cn, T en, T Sn,
-                                  const Pt64<T>& pn, T hds, double ds64, T I, bool to_origin) {
+__device__ inline void emit_point(const ItemCtx& c, SweepState<T>& st, Emitter<T>& em, T cn, T en,
+                                  const Pt64<T>& pn, T hds, double ds64, T I) {
     if (em.have) {
-        T ic;
         if (c.dtau_rcp > 0.0)
-            ic = substep_interval<T, SCH>(c, st, em.first, em.c, em.e, em.S, cn, en, hds, em.p, pn, ds64, I,
-                                          to_origin);
-        else ic = near_row<T, SCH>(st, em.first, (em.c + cn) * hds, em.S, em.c, em.e, cn, en, I, to_origin);
-        if (SCH == 0) Sn = en * ic;
+            substep_interval<T, SCH>(c, st, em.first, em.c, em.e, cn, en, hds, em.p, pn, ds64, I);
+        else row_s<T, SCH>(st, em.first, (em.c + cn) * hds, em.c, em.e, cn, en, I);
         em.first = false;
-    } else if (SCH == 0) {
-        Sn = en * row_rc<T>(st, (T)0, (T)0, cn);
     }
     em.c = cn;
     em.e = en;
-    em.S = Sn;
     em.p = pn;
     em.have = true;
 }
@@ -459,20 +438,19 @@ __device__ inline void emit_point(const ItemCtx& c, SweepState<T>& st, Emitter<T
 // A list point (real) of the current side, as the refinement needs it.
 template <typename T>
 struct RealPt {
-    T c, e, S;
+    T c, e;
     Pt64<T> p;
     double dot;   // projected velocity n.(v - v_o)
     int64_t row;  // table row offset in bytes
 };
 
-// Interval from real point P (far) to real point C (near), hds / ds64 its half
-// and FP64 lengths: velocity sub-points first (m from |p_C - p_P|), each emitted,
+// Interval from real point P (far) to real point C (near), hds / ds64 its length
+// times half_step and FP64 length: velocity sub-points first (m from |p_C - p_P|), each emitted,
 // then C itself.  fwd: this side is the +n ray, whose nearer point has the
 // smaller line coordinate (so it is the interval's point a).
 template <typename T, bool UDX, int SCH>
 __device__ inline void real_interval(const ItemCtx& c, SweepState<T>& st, Emitter<T>& em, const RealPt<T>& P,
-                                     const RealPt<T>& C, T hds, double ds64, bool fwd, const LaneFreq& lf, T I,
-                                     bool to_origin) {
+                                     const RealPt<T>& C, T hds, double ds64, bool fwd, const LaneFreq& lf, T I) {
     int m = 1;
     if (c.dv_rcp > 0.0) {
         double q = ceil(fabs(C.dot - P.dot) * c.dv_rcp);
@@ -481,7 +459,7 @@ __device__ inline void real_interval(const ItemCtx& c, SweepState<T>& st, Emitte
         m = __builtin_amdgcn_readfirstlane(m);  // the same in every lane
     }
     if (m == 1) {
-        emit_point<T, SCH>(c, st, em, C.c, C.e, C.S, C.p, hds, ds64, I, to_origin);
+        emit_point<T, SCH>(c, st, em, C.c, C.e, C.p, hds, ds64, I);
         return;
     }
     const T hs = hds * rcp<T>((T)m);
@@ -513,10 +491,9 @@ __device__ inline void real_interval(const ItemCtx& c, SweepState<T>& st, Emitte
         const T ya = fma_<T>(t, g1 - g0, g0), yb = fma_<T>(t, h1 - h0, h0);
         const T cv = fma_<T>(wt, xb - xa, xa);
         const T ev = fma_<T>(wt, yb - ya, ya);
-        emit_point<T, SCH>(c, st, em, cv, ev, SCH == 0 ? (T)0 : ev * rcp<T>(cv), Pt64<T>{a0, a1, b0, b1, t64, w},
-                           hs, ds64s, I, false);
+        emit_point<T, SCH>(c, st, em, cv, ev, Pt64<T>{a0, a1, b0, b1, t64, w}, hs, ds64s, I);
     }
-    emit_point<T, SCH>(c, st, em, C.c, C.e, C.S, C.p, hs, ds64s, I, to_origin);
+    emit_point<T, SCH>(c, st, em, C.c, C.e, C.p, hs, ds64s, I);
 }
 
 // One side of the line with velocity sampling and/or optical-depth sub-steps
@@ -528,18 +505,13 @@ constexpr int REF_STAGE_WORDS = 12;
 
 template <typename T, bool MOVING, bool UDX, int SCH>
 __device__ inline void sweep_ref(const ItemCtx& c, int64_t base, int n, const LaneFreq& lf, int lane, bool fwd,
-                                 T chi_o, T eta_o, T S_o, T I, SweepState<T>& st, uint32_t* stage) {
+                                 T chi_o, T eta_o, T I, SweepState<T>& st, uint32_t* stage) {
     Emitter<T> em;
     RealPt<T> prev{};
     T hds_prev = (T)0;
     double ds64_prev = 0.0;
     int done = 0;
-    if (SCH == 0) {  // the state before the far end (row_rc)
-        st.G = (T)1;
-        st.r = (T)1;
-        st.a = (T)0;
-        st.Y = I;
-    }
+    if (SCH == 0) row2_start<T>(st.s, I);
     const uint32_t lane_off = (uint32_t)lf.f * (uint32_t)sizeof(T);
     const int lb_bytes = (lf.fb + lf.fl) * (int)sizeof(T);
     const int lo_bytes = lf.fb * (int)sizeof(T);
@@ -630,12 +602,11 @@ __device__ inline void sweep_ref(const ItemCtx& c, int64_t base, int n, const La
                 cur.e = f.ea;
                 cur.p = Pt64<T>{cur.c, cur.c, cur.c, cur.c, 0.0, 0.0};
             }
-            cur.S = SCH == 0 ? (T)0 : cur.e * rcp<T>(cur.c);  // SCH 0: formed with the row (emit_point)
-            if (done == 0) emit_point<T, SCH>(c, st, em, cur.c, cur.e, cur.S, cur.p, (T)0, 0.0, I, false);
-            else real_interval<T, UDX, SCH>(c, st, em, prev, cur, hds_prev, ds64_prev, fwd, lf, I, false);
+            if (done == 0) emit_point<T, SCH>(c, st, em, cur.c, cur.e, cur.p, (T)0, 0.0, I);
+            else real_interval<T, UDX, SCH>(c, st, em, prev, cur, hds_prev, ds64_prev, fwd, lf, I);
             prev = cur;
             ds64_prev = ds64;
-            hds_prev = (T)0.5 * (T)ds64;
+            hds_prev = (T)(half_step<SCH>() * ds64);
             ++done;
         }
         __builtin_amdgcn_wave_barrier();  // every lane has read this run before the next is staged
@@ -644,11 +615,10 @@ __device__ inline void sweep_ref(const ItemCtx& c, int64_t base, int n, const La
         RealPt<T> org;
         org.c = chi_o;
         org.e = eta_o;
-        org.S = S_o;
         org.p = Pt64<T>{chi_o, chi_o, chi_o, chi_o, 0.0, 0.0};
         org.dot = 0.0;
         org.row = c.row_o;
-        real_interval<T, UDX, SCH>(c, st, em, prev, org, hds_prev, ds64_prev, fwd, lf, I, true);
+        real_interval<T, UDX, SCH>(c, st, em, prev, org, hds_prev, ds64_prev, fwd, lf, I);
     }
 }
 
@@ -677,14 +647,9 @@ constexpr int STAGE_WORDS = 8;
 template <typename T, bool MOVING, bool UDX, int GROUP, bool SMALL, int SCH>
 __device__ inline void sweep(const ItemCtx& c, int64_t base, int n, const LaneFreq& lf, int lane, T chi_o, T eta_o,
                              T I, SweepState<T>& st, uint32_t* stage) {
-    T c_prev = (T)0, e_prev = (T)0, S_prev = (T)0, ds_prev = (T)0;
+    T c_prev = (T)1, e_prev = (T)0, ds_prev = (T)0;  // before the first point: a row that changes nothing
     int done = 0;
-    if (SCH == 0) {  // the state before the far end (row_rc)
-        st.G = (T)1;
-        st.r = (T)1;
-        st.a = (T)0;
-        st.Y = I;
-    }
+    if (SCH == 0) row2_start<T>(st.s, I);
     const uint32_t lane_off = (uint32_t)lf.f * (uint32_t)sizeof(T);
     // the lane's own frequency and its block's first and last, in bytes
     const int lb_bytes = (lf.fb + lf.fl) * (int)sizeof(T);
@@ -703,7 +668,7 @@ __device__ inline void sweep(const ItemCtx& c, int64_t base, int n, const LaneFr
             const uint64_t row = (uint64_t)q * (uint64_t)c.ld_bytes;
             const double z = c.Zr[base + e];
             const double zi = e > 0 ? c.Zr[base + e - 1] : 0.0;
-            const T ds = (T)0.5 * (T)(z - zi);  // half the difference of FP64 projections, rounded once
+            const T ds = (T)(half_step<SCH>() * (z - zi));  // from the difference of FP64 projections
             w[0] = (uint32_t)row;
             w[1] = (uint32_t)(row >> 32);
             if (MOVING) {
@@ -782,14 +747,9 @@ __device__ inline void sweep(const ItemCtx& c, int64_t base, int n, const LaneFr
                         cc = ca[g];
                         et = ea[g];
                     }
-                    if (SCH == 0) {
-                        // the row and this point's 1/chi from one reciprocal; at the first point
-                        // c_prev and ds_prev are 0, so dt = 0 (see row_rc)
-                        const T dt = (c_prev + cc) * ds_prev;  // ds_prev holds ds/2
-                        S_prev = et * row_rc<T>(st, dt, S_prev, cc);
-                    } else if (done > 0) {
-                        const T dt = (c_prev + cc) * ds_prev;
-                        row_s<T, SCH>(st, done == 1, dt, S_prev, c_prev, e_prev, cc, et, I);
+                    if (SCH == 0 || done > 0) {
+                        const T dt = (c_prev + cc) * ds_prev;  // ds_prev holds ds times half_step
+                        row_s<T, SCH>(st, done == 1, dt, c_prev, e_prev, cc, et, I);
                     }
                     c_prev = cc;
                     e_prev = et;
@@ -803,10 +763,7 @@ __device__ inline void sweep(const ItemCtx& c, int64_t base, int n, const LaneFr
         if (j < cnt) point_group(std::false_type{}, j);
         __builtin_amdgcn_wave_barrier();  // every lane has read this run before the next is staged
     }
-    if (n > 0) {
-        const T dt = (c_prev + chi_o) * ds_prev;
-        row_s<T, SCH>(st, n == 1, dt, S_prev, c_prev, e_prev, chi_o, eta_o, I);
-    }
+    if (SCH == 0 || n > 0) row_s<T, SCH>(st, n == 1, (c_prev + chi_o) * ds_prev, c_prev, e_prev, chi_o, eta_o, I);
 }
 
 // ---------------------------------------------------------------- packed half waves
@@ -821,15 +778,12 @@ __device__ inline void sweep(const ItemCtx& c, int64_t base, int n, const LaneFr
 // the arithmetic of every lane is that of `sweep`, so u is the same bit for bit.
 template <typename T, bool MOVING, bool UDX, int GROUP>
 __device__ inline void sweep_half(const ItemCtx& c, double nx, double ny, double nz, int64_t base, int n,
-                                  const LaneFreq& lf, int lane, T chi_o, T I, SweepState<T>& st,
+                                  const LaneFreq& lf, int lane, T chi_o, T I, Row2<T>& st,
                                   uint32_t* stage) {
     const int hl = lane & 31;
     uint32_t* my = stage + (lane >> 5) * 32 * STAGE_WORDS;
-    T c_prev = (T)0, S_prev = (T)0, ds_prev = (T)0;
-    st.G = (T)1;  // the state before the far end (row_rc)
-    st.r = (T)1;
-    st.a = (T)0;
-    st.Y = I;
+    T c_prev = (T)1, e_prev = (T)0, ds_prev = (T)0;
+    row2_start<T>(st, I);
     const uint32_t lane_off = (uint32_t)lf.f * (uint32_t)sizeof(T);
     const int lb_bytes = (lf.fb + lf.fl) * (int)sizeof(T);
     const int lbm_bytes = lb_bytes - (int)sizeof(T);
@@ -850,7 +804,7 @@ __device__ inline void sweep_half(const ItemCtx& c, double nx, double ny, double
             const uint64_t row = (uint64_t)q * (uint64_t)c.ld_bytes;
             const double z = c.Zr[base + e];
             const double zi = e > 0 ? c.Zr[base + e - 1] : 0.0;
-            const T ds = (T)0.5 * (T)(z - zi);
+            const T ds = (T)(HALF_STEP2 * (z - zi));
             w[0] = (uint32_t)row;
             w[1] = (uint32_t)(row >> 32);
             if (MOVING) {
@@ -921,9 +875,9 @@ __device__ inline void sweep_half(const ItemCtx& c, double nx, double ny, double
                         cc = ca[g];
                         et = ea[g];
                     }
-                    const T dt = (c_prev + cc) * ds_prev;
-                    S_prev = et * row_rc<T>(st, dt, S_prev, cc);
+                    row2<T>(st, (c_prev + cc) * ds_prev, c_prev, e_prev);
                     c_prev = cc;
+                    e_prev = et;
                     ds_prev = dsv[g];
                 }
             }
@@ -933,7 +887,7 @@ __device__ inline void sweep_half(const ItemCtx& c, double nx, double ny, double
         for (; j0 < cnt_max; j0 += GROUP) half_group(std::false_type{}, j0);
         __builtin_amdgcn_wave_barrier();  // every lane has read this run before the next is staged
     }
-    if (n > 0) row<T>(st, n == 1, (c_prev + chi_o) * ds_prev, S_prev, I);
+    row2<T>(st, (c_prev + chi_o) * ds_prev, c_prev, e_prev);
 }
 
 // The packed item of pairs r, r+1 (r even), frequencies 64.. of each (see sweep_half).
@@ -971,10 +925,10 @@ __device__ inline void solve_item_half(const SolveLaunch& a, int64_t oi, int64_t
     const T chi_o = ((const T*)a.chi)[o * a.ld + lf.f];
     const T eta_o = ((const T*)a.eta)[o * a.ld + lf.f];
     const T S_o = eta_o * rcp<T>(chi_o);
-    SweepState<T> m{}, p{};
+    Row2<T> m, p;
     sweep_half<T, MOVING, UDX, GROUP>(c, nx, ny, nz, bm, nm, lf, lane, chi_o, I, m, stage);
     sweep_half<T, MOVING, UDX, GROUP>(c, nx, ny, nz, bp, np, lf, lane, chi_o, I, p, stage);
-    const T u = origin_u<T>(nm > 0, np > 0, m, p, S_o, I);
+    const T u = origin_u<T>(nm + np > 0, m.a, m.G * m.r, m.Y, p.a, p.G * p.r, p.Y, S_o, I);
     if (lf.active) {
         ((T*)a.u)[(oi * a.R + rh) * a.F + lf.f] = u;
         if (!(u == u) || u - u != (T)0) atomicOr(a.err, ERRBIT_NONFINITE);
@@ -1032,8 +986,8 @@ __device__ inline void solve_item(const SolveLaunch& a, int64_t w, int nfc, int 
     const T S_o = eta_o * rcp<T>(chi_o);
     SweepState<T> m{}, p{};
     if (REF) {
-        sweep_ref<T, MOVING, UDX, SCH>(c, bm, nm, lf, lane, false, chi_o, eta_o, S_o, I, m, stage);
-        sweep_ref<T, MOVING, UDX, SCH>(c, bp, np, lf, lane, true, chi_o, eta_o, S_o, I, p, stage);
+        sweep_ref<T, MOVING, UDX, SCH>(c, bm, nm, lf, lane, false, chi_o, eta_o, I, m, stage);
+        sweep_ref<T, MOVING, UDX, SCH>(c, bp, np, lf, lane, true, chi_o, eta_o, I, p, stage);
     } else {
         if (a.small_tables) {
             sweep<T, MOVING, UDX, GROUP, true, SCH>(c, bm, nm, lf, lane, chi_o, eta_o, I, m, stage);
@@ -1051,7 +1005,7 @@ __device__ inline void solve_item(const SolveLaunch& a, int64_t w, int nfc, int 
             if (lf.active) atomicOr(a.err, ERRBIT_STEP);
         }
     } else {
-        u = origin_u<T>(nm > 0, np > 0, m, p, S_o, I);
+        u = origin_u<T>(nm + np > 0, m.s.a, m.s.G * m.s.r, m.s.Y, p.s.a, p.s.G * p.s.r, p.s.Y, S_o, I);
     }
     if (lf.active) {
         ((T*)a.u)[(oi * a.R + r) * a.F + lf.f] = u;
@@ -1124,6 +1078,489 @@ __global__ __launch_bounds__(SOLVE_BLOCK) void k_solve_persist(const SolveLaunch
             const int64_t w = a.items ? (int64_t)a.items[it] : it;
             solve_item<T, MOVING, UDX, GROUP, REF, SCH, PACK>(a, w, nfc, lane, stage);
         }
+    }
+}
+
+// ---------------------------------------------------------------- several lines per wave
+//
+// The second-order sweep of plain lines with V consecutive frequencies per lane
+// (FP32: 4 or 3, FP64: 2), so a line of F frequencies takes LPL = F/V lanes and
+// a wave NL = 64/LPL lines, consecutive items of the schedule.  A lane reads
+// its V values of a row with one load of up to 16 bytes, and what is the same
+// for every frequency of a point (the LDS record, the shift, the address) is
+// formed once per V frequencies instead of once per frequency.
+//
+// Moving media read the point's row at f - k - 1 and f - k clamped to the
+// block, so a lane needs V + 1 consecutive values of the row but loads V: the
+// ones from f0 - k - 1 on when k < 0, from f0 - k on when k >= 0.  The missing
+// one is the next lane's first (k < 0) or the previous lane's last (k >= 0), and
+// in the last (first) lane of the block, where both lie beyond the block's
+// edge, its own: a wave shift by one lane instead of a load (a second load of
+// lines just asked for stalls the L1 on the pending miss).  Which side it is on
+// is a scalar branch where the wave's lines agree, selects where they do not.
+// The tables are the plan's padded copies (k_pad_tables): each block's edge
+// values repeated V times on both sides, so that clamping the window's start to
+// [-V, L] gives every one of its values clamped.  16-byte loads at 4-byte
+// alignment cost what aligned ones do once the rows come from L2 (measured over
+// random rows).  Static media read the caller's tables directly.
+//
+// The arithmetic of every frequency is that of `sweep`, operation for
+// operation: u is the same bit for bit.
+//
+// Neighbouring items have lines of similar length, but their origins sit
+// anywhere along them, so a wave that took side after side would run each for
+// its longest.  A line is therefore one run of points: the -n_r side from its
+// far end, the origin, the +n_r side from its far end, the origin again.  The
+// first time the origin has been reached the side's result is put aside (LDS)
+// and the state starts anew; that is a branch of its own, taken twice per line.
+// The lanes of a line stage STAGE_PER_LANE points each, one dependent round trip
+// to memory (ids and Z, then velocities) for what is mostly the whole run;
+// points that every line of the wave has carry no test.  The loads of LINE_DEPTH
+// points are in flight ahead of their rows.
+//
+// Bound: VALU issue and the L1's data path side by side.  Per wave and point 71
+// instructions, 4 of them reciprocals, and two 1-KiB loads, for 256
+// point-frequencies; at V = 4 the issue alone is 8.2 ms and the loads alone
+// 5.9 ms (L1 hits) to 7.8 ms (L2) of the 11.7 ms that the 50k-point wind's sweep
+// takes (96 pairs, 64 frequencies).  Measured, one line per wave against this
+// kernel: that wind 11.8 -> 11.7 ms, in FP64 with 20k points and 24 pairs 2.41 ->
+// 1.62 ms; a 50k-point grid with 2 x 48 frequencies and 96 pairs 36.0 -> 28.4 ms;
+// a batch of 16 clouds 13.4 -> 13.2 ms; a static cloud of 1200 points in FP64 (31
+// frequencies, 6 pairs) 20 -> 15 us.  Not taken (wind and grid, ms): loads 1
+// point ahead 14.1 and 34.8, 3 ahead 12.7 and 28.4 (spills at V = 4); 5 waves per
+// SIMD 14.0 and 29.4 (spills); V = 2 in FP32 12.9 and 38.6.
+template <typename T, int V>
+struct WinOf;
+template <>
+struct WinOf<float, 4> {
+    typedef float type __attribute__((ext_vector_type(4), aligned(4)));
+};
+template <>
+struct WinOf<float, 3> {
+    typedef float type __attribute__((ext_vector_type(3), aligned(4)));
+};
+template <>
+struct WinOf<double, 2> {
+    typedef double type __attribute__((ext_vector_type(2), aligned(8)));
+};
+
+// The next or previous lane's value (beyond the wave's end: undefined; a block's last or first
+// lane replaces it).
+constexpr int DPP_WAVE_SHL1 = 0x130, DPP_WAVE_SHR1 = 0x138;
+template <int CTRL>
+__device__ inline float lane_shift(float v) {
+    return __builtin_bit_cast(float, __builtin_amdgcn_update_dpp(0, __builtin_bit_cast(int, v), CTRL, 0xF, 0xF, true));
+}
+template <int CTRL>
+__device__ inline double lane_shift(double v) {
+    int2 p = __builtin_bit_cast(int2, v);
+    p.x = __builtin_amdgcn_update_dpp(0, p.x, CTRL, 0xF, 0xF, true);
+    p.y = __builtin_amdgcn_update_dpp(0, p.y, CTRL, 0xF, 0xF, true);
+    return __builtin_bit_cast(double, p);
+}
+
+// x[0..V]: the V + 1 consecutive values of a lane whose load gave v: all but the last (up = false) or all
+// but the first (up = true).
+template <typename T, int V, typename Win>
+__device__ inline void window_lo(const Win& v, bool last, T (&x)[V + 1]) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) x[i] = v[i];
+    const T n = lane_shift<DPP_WAVE_SHL1>((T)v[0]);
+    x[V] = last ? (T)v[V - 1] : n;
+}
+template <typename T, int V, typename Win>
+__device__ inline void window_up(const Win& v, bool first, T (&x)[V + 1]) {
+#pragma unroll
+    for (int i = 0; i < V; ++i) x[i + 1] = v[i];
+    const T p = lane_shift<DPP_WAVE_SHR1>((T)v[V - 1]);
+    x[0] = first ? (T)v[0] : p;
+}
+template <typename T, int V, typename Win>
+__device__ inline void window_any(const Win& v, bool up, bool first, bool last, T (&x)[V + 1]) {
+    T a[V + 1], b[V + 1];
+    window_lo<T, V>(v, last, a);
+    window_up<T, V>(v, first, b);
+#pragma unroll
+    for (int i = 0; i <= V; ++i) x[i] = up ? b[i] : a[i];
+}
+
+// A lane's part of its line.
+struct LineLane {
+    int line, li;   // line of the wave, lane of the line
+    bool used;      // takes part in its line (false: repeats another lane's work, stages and stores nothing)
+    int f0;         // its first frequency
+    int nf;         // how many of its V it stores (0: past the line's end, or a chunk's outer lanes)
+    int win;        // padded-row column of f0
+    int lo, hi;     // bounds of a window's start (columns)
+    bool first, last;  // first, last lane of its block
+    double dx;
+};
+
+template <int V, bool MOVING>
+__device__ inline LineLane line_lane(const SolveLaunch& a, int lane, int chunk) {
+    LineLane l;
+    const int lpl = a.lpl;
+    l.line = lane / lpl;
+    l.li = lane - l.line * lpl;
+    l.used = l.line < a.lines;
+    if (!l.used) {
+        l.line = a.lines - 1;
+        l.li = 0;
+    }
+    int li = l.li + chunk * 64;
+    bool store = true;
+    if (MOVING && a.line_chunks > 1) {  // a chunk's outer lanes only lend their values to their neighbours
+        li = l.li - 1 + chunk * 62;
+        li = li < 0 ? 0 : li;
+        store = l.li > 0 && l.li < 63;
+    }
+    l.dx = a.dx[0];
+    if (!MOVING) {  // the last lane steps back to stay inside the row (a.F >= V): it shares values with its neighbour
+        l.f0 = li * V < a.F - V ? li * V : a.F - V;
+        l.nf = li * V < a.F ? V : 0;
+        l.win = l.lo = l.hi = 0;
+        l.first = l.last = false;
+        return l;
+    }
+    int fb = 0, L = a.blk_start[1], col = V, b_lanes = (L + V - 1) / V;  // block: first frequency, length, column, lanes
+    bool found = li < b_lanes;
+#pragma unroll
+    for (int b = 1; b < RT_MAX_FREQ_BLOCKS; ++b)
+        if (!found && b < a.n_blocks) {
+            li -= b_lanes;
+            col += L + 2 * V;
+            fb = a.blk_start[b];
+            L = a.blk_start[b + 1] - fb;
+            b_lanes = (L + V - 1) / V;
+            l.dx = a.dx[b];
+            found = li < b_lanes;
+        }
+    if (!found) {  // past the line's last lane
+        store = false;
+        li = b_lanes - 1;
+    }
+    l.f0 = fb + li * V;
+    l.nf = !store ? 0 : L - li * V < V ? L - li * V : V;
+    l.win = col + li * V;
+    l.lo = col - V;
+    l.hi = col + L;
+    l.first = li == 0;
+    l.last = li == b_lanes - 1;
+    return l;
+}
+
+constexpr int MAX_LINES = 16;  // lines of a wave
+constexpr int LINE_DEPTH = 2;  // points whose loads are in flight
+constexpr int LINE_WORDS(int es) { return es == 4 ? 4 : 8; }  // 32-bit words of a staged point
+constexpr int STAGE_PER_LANE(int es) { return es == 4 ? 4 : 2; }
+// What staging needs of a line, in LDS: the pair's direction (FP64), the origin's velocity.
+constexpr int LINE_CONST_WORDS = 10;
+
+// A wave's LDS: staged points (the lines' records one apart, in other banks), line constants, the first
+// side's results [3][V][64].
+template <typename T, int V>
+struct LineLds {
+    uint32_t stage[(64 * STAGE_PER_LANE(sizeof(T)) + MAX_LINES) * LINE_WORDS(sizeof(T))];
+    uint32_t consts[MAX_LINES * LINE_CONST_WORDS];
+    T first[3 * V * 64];
+};
+
+template <typename T>
+__device__ inline T line_I(const SolveLaunch& a, int f) {
+    return (T)a.I_bc[f < a.F ? f : a.F - 1];
+}
+
+// The lines of one wave, lane by lane: pair r of origin position oi (live: there is one).
+template <typename T, int V, bool MOVING, bool UDX>
+__device__ inline void solve_lines(const SolveLaunch& a, bool live, int64_t oi, int64_t r, const LineLane& l,
+                                   LineLds<T, V>& lds) {
+    typedef typename WinOf<T, V>::type Win;
+    constexpr int WORDS = LINE_WORDS(sizeof(T));
+    constexpr int SH = sizeof(T) == 4 ? 2 : 3, D = LINE_DEPTH;
+    const int lane = threadIdx.x & 63, lpl = a.lpl;
+    int64_t o = a.origins ? (int64_t)a.origins[oi] : oi;
+    bool lists = true;
+    if (o < 0 || o >= a.P) {  // an invalid id: a line of the origin alone, of point 0, stored nowhere
+        if (live && l.used && l.li == 0) atomicOr(a.err, ERRBIT_ORIGIN);
+        live = false;
+        lists = false;
+        o = 0;
+    }
+    const int64_t slot = oi * 2 * a.R + 2 * r;
+    const int64_t bp = a.ray_off[slot], bm = a.ray_off[slot + 1], be = a.ray_off[slot + 2];
+    const int np = lists ? (int)(bm - bp) : 0, nm = lists ? (int)(be - bm) : 0;
+    const int n = np + nm + 2;  // points of the run
+    uint32_t* lc = lds.consts + l.line * LINE_CONST_WORDS;
+    if (MOVING) {
+        const double* dv = a.dirs + 3 * ((a.per_origin ? oi * a.R : 0) + r);
+        for (int c = l.li; c < 3; c += lpl) {
+            ((double*)lc)[c] = dv[c];
+            ((float*)(lc + 6))[c] = a.vel[3 * o + c];
+        }
+    }
+    constexpr int K = STAGE_PER_LANE(sizeof(T));
+    const int run = K * lpl;  // points staged at a time
+    uint32_t* seg = lds.stage + (l.line * run + l.line) * WORDS;
+    const uint32_t row_bytes = (uint32_t)((MOVING ? a.pad_ld : (int)a.ld) * (int)sizeof(T));
+    const char* tc = (const char*)(MOVING ? a.pad_chi : a.chi);
+    const char* te = (const char*)(MOVING ? a.pad_eta : a.eta);
+    Row2<T> st[V];
+    T pc[V], pe[V], ds_prev;  // the last point's optics and step factor
+    auto start = [&]() {
+#pragma unroll
+        for (int i = 0; i < V; ++i) {
+            row2_start<T>(st[i], line_I<T>(a, l.f0 + i));
+            pc[i] = (T)1;
+            pe[i] = (T)0;
+        }
+        ds_prev = (T)0;
+    };
+    start();
+    int n_min = n, n_max = n;
+    for (int g = 0; g < a.lines; ++g) {
+        const int v = __builtin_amdgcn_readlane(n, g * lpl);
+        n_min = g == 0 || v < n_min ? v : n_min;
+        n_max = g == 0 || v > n_max ? v : n_max;
+    }
+    n_min = uni(n_min);
+    n_max = uni(n_max);
+    __builtin_amdgcn_wave_barrier();
+    for (int j0 = 0; j0 < n_max; j0 += run) {
+        // lane li stages points j0 + li + k lpl of its line's run: place in the ray lists (none: the origin)
+        int q[K];
+        double len[K];
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            const int js = j0 + l.li + k * lpl;
+            const bool minus = js < nm;
+            const int e = minus ? nm - 1 - js : np + nm - js;
+            q[k] = (int)o;
+            len[k] = 0.0;
+            if (js < n && js != nm && e >= 0) {
+                const int64_t at = (minus ? bm : bp) + e;
+                q[k] = a.ray_ids[at];
+                const double z = a.ray_Z[at];
+                len[k] = e > 0 ? z - a.ray_Z[at - 1] : z;
+            }
+        }
+#pragma unroll
+        for (int k = 0; k < K; ++k) {
+            if (!l.used || j0 + l.li + k * lpl >= n) continue;
+            uint32_t* w = seg + (l.li + k * lpl) * WORDS;
+            const T ds = (T)(HALF_STEP2 * len[k]);  // from the difference of FP64 projections
+            w[0] = (uint32_t)q[k] * row_bytes;
+            *(T*)(w + (sizeof(T) == 4 ? 1 : 2)) = ds;
+            if (MOVING) {
+                const float* vq = a.vel + 3 * (int64_t)q[k];
+                const float* vo = (const float*)(lc + 6);
+                const double* nr = (const double*)lc;
+                const double dvx = (double)vq[0] - (double)vo[0];
+                const double dvy = (double)vq[1] - (double)vo[1];
+                const double dvz = (double)vq[2] - (double)vo[2];
+                const double dot = (nr[0] * dvx + nr[1] * dvy) + nr[2] * dvz;
+                if (UDX) {
+                    const double delta = dot / a.dx[0];
+                    const double kf = floor(delta);
+                    w[sizeof(T) == 4 ? 2 : 1] = (uint32_t)(int)kf;
+                    *(T*)(w + (sizeof(T) == 4 ? 3 : 4)) = (T)(delta - kf);
+                } else {
+                    *(double*)(w + (sizeof(T) == 4 ? 2 : 4)) = dot;
+                }
+            }
+        }
+        __builtin_amdgcn_wave_barrier();
+        const int cnt = n - j0 < run ? n - j0 : run;  // this line's points of the run (0 or less: it has ended)
+        const int turn = nm - j0;                     // the point at which its first side ends
+        const int end = n_max - j0 < run ? n_max - j0 : run;
+        const int full = n_min - j0 < run ? n_min - j0 : run;
+        // D points in flight: their loads are issued D points ahead of their rows.  Past a line's
+        // end its last staged point is read again.
+        Win wc[D], we[D];
+        T tt[D], ds[D];
+        bool up[D];
+        const int top = cnt > 0 ? cnt - 1 : 0;
+        auto load = [&](int d, int j) {
+            const uint32_t* w = seg + (j < top ? j : top) * WORDS;
+            const uint4 r0 = *(const uint4*)w;
+            ds[d] = sizeof(T) == 4 ? (T)__builtin_bit_cast(float, r0.y)
+                                   : (T)__builtin_bit_cast(double, ((uint64_t)r0.w << 32) | r0.z);
+            uint32_t at;
+            if (MOVING) {
+                int k;
+                if (UDX) {
+                    k = (int)(sizeof(T) == 4 ? r0.z : r0.y);
+                    tt[d] = sizeof(T) == 4 ? (T)__builtin_bit_cast(float, r0.w) : *(const T*)(w + 4);
+                } else {  // per-lane block widths: the shift as the oracle forms it, a division
+                    const double dot = sizeof(T) == 4 ? __builtin_bit_cast(double, ((uint64_t)r0.w << 32) | r0.z)
+                                                      : *(const double*)(w + 4);
+                    const double delta = dot / l.dx;
+                    const double kf = floor(delta);
+                    k = (int)kf;
+                    tt[d] = (T)(delta - kf);
+                }
+                up[d] = k >= 0;
+                at = r0.x + ((uint32_t)clamp_i32(l.win - (up[d] ? k : k + 1), l.lo, l.hi) << SH);
+            } else {
+                at = r0.x + ((uint32_t)l.f0 << SH);
+            }
+            wc[d] = *(const Win*)(tc + at);
+            we[d] = *(const Win*)(te + at);
+        };
+        auto step = [&](auto all, int d, int j) {
+            constexpr bool ALL = decltype(all)::value;  // every line of the wave has this point
+            if (!ALL && j >= cnt) return;
+            auto rows = [&](const T (&xc)[V + 1], const T (&xe)[V + 1]) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    T cc = xc[i], et = xe[i];
+                    if (MOVING) {
+                        cc = fma_<T>(tt[d], xc[i] - xc[i + 1], xc[i + 1]);
+                        et = fma_<T>(tt[d], xe[i] - xe[i + 1], xe[i + 1]);
+                    }
+                    row2<T>(st[i], (pc[i] + cc) * ds_prev, pc[i], pe[i]);
+                    pc[i] = cc;
+                    pe[i] = et;
+                }
+            };
+            T xc[V + 1], xe[V + 1];
+            if (!MOVING) {
+#pragma unroll
+                for (int i = 0; i < V; ++i) {
+                    xc[i] = wc[d][i];
+                    xe[i] = we[d][i];
+                }
+                rows(xc, xe);
+            } else if (ALL && !__builtin_amdgcn_ballot_w64(up[d])) {
+                window_lo<T, V>(wc[d], l.last, xc);
+                window_lo<T, V>(we[d], l.last, xe);
+                rows(xc, xe);
+            } else if (ALL && !__builtin_amdgcn_ballot_w64(!up[d])) {
+                window_up<T, V>(wc[d], l.first, xc);
+                window_up<T, V>(we[d], l.first, xe);
+                rows(xc, xe);
+            } else {
+                window_any<T, V>(wc[d], up[d], l.first, l.last, xc);
+                window_any<T, V>(we[d], up[d], l.first, l.last, xe);
+                rows(xc, xe);
+            }
+            ds_prev = ds[d];
+            if (__builtin_amdgcn_ballot_w64(j == turn))
+                if (j == turn) {  // the first side has reached the origin
+#pragma unroll
+                    for (int i = 0; i < V; ++i) {
+                        lds.first[(3 * i + 0) * 64 + lane] = st[i].a;
+                        lds.first[(3 * i + 1) * 64 + lane] = st[i].G * st[i].r;
+                        lds.first[(3 * i + 2) * 64 + lane] = st[i].Y;
+                    }
+                    start();
+                }
+        };
+#pragma unroll
+        for (int d = 0; d < D; ++d) load(d, d);
+        int j = 0;
+        for (; j + D <= full; j += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                step(std::true_type{}, d, j + d);
+                load(d, j + d + D);
+            }
+        }
+        for (; j < end; j += D) {
+#pragma unroll
+            for (int d = 0; d < D; ++d) {
+                step(std::false_type{}, d, j + d);
+                load(d, j + d + D);
+            }
+        }
+        __builtin_amdgcn_wave_barrier();  // every lane has read this run before the next is staged
+    }
+    if (live && l.used) {
+        T* u = (T*)a.u + (oi * a.R + r) * a.F + l.f0;
+        bool bad = false;
+#pragma unroll
+        for (int i = 0; i < V; ++i) {  // the last point was the origin
+            const T v = origin_u<T>(np + nm > 0, lds.first[(3 * i + 0) * 64 + lane], lds.first[(3 * i + 1) * 64 + lane],
+                                    lds.first[(3 * i + 2) * 64 + lane], st[i].a, st[i].G * st[i].r, st[i].Y,
+                                    pe[i] * rcp<T>(pc[i]), line_I<T>(a, l.f0 + i));
+            if (i < l.nf) {
+                u[i] = v;
+                bad = bad || !(v == v) || v - v != (T)0;
+            }
+        }
+        if (bad) atomicOr(a.err, ERRBIT_NONFINITE);
+    }
+}
+
+// Workgroups of the direct launch take runs of XCD_RUN_LINES blocks per XCD.
+template <typename T, int V, bool MOVING, bool UDX, bool PERSIST>
+__global__ __launch_bounds__(SOLVE_BLOCK, 4) void k_solve_lines(const SolveLaunch a) {
+    __shared__ __attribute__((aligned(16))) LineLds<T, V> lds_all[WAVES_PER_BLOCK];
+    LineLds<T, V>& lds = lds_all[threadIdx.x >> 6];
+    const int lane = threadIdx.x & 63;
+    const int64_t n_pairs = a.n_origins * a.R;
+    const int nfc = (a.F + 63) / 64;                   // chunks of the items' numbering
+    const int64_t units = (n_pairs + a.lines - 1) / a.lines * a.line_chunks;  // waves' worth of work
+    auto unit = [&](int64_t w) {
+        const int chunk = a.line_chunks == 1 ? 0 : (int)(w % a.line_chunks);
+        const int64_t t0 = w / a.line_chunks * a.lines;  // the wave's first item of the schedule
+        const LineLane l = line_lane<V, MOVING>(a, lane, chunk);
+        const bool live = t0 + l.line < n_pairs;
+        const int64_t t = live ? t0 + l.line : n_pairs - 1;  // past the end: the last item again, stored nowhere
+        int64_t oi, r;
+        if (a.items) {
+            const uint32_t pr = (uint32_t)a.items[t * nfc] / (uint32_t)nfc;
+            oi = pr / (uint32_t)a.R;
+            r = pr - (uint32_t)oi * (uint32_t)a.R;
+        } else {  // one division per wave: the lines of a wave follow one another
+            const int64_t inner = a.order ? a.n_origins : a.R;
+            int64_t hi = t0 / inner, lo = t0 - hi * inner + (t - t0);
+            while (lo >= inner) {
+                lo -= inner;
+                ++hi;
+            }
+            r = a.order ? hi : lo;
+            oi = !a.order ? hi : (int64_t)(a.pair_order ? a.pair_order[t] : a.order[lo]);
+        }
+        solve_lines<T, V, MOVING, UDX>(a, live, oi, r, l, lds);
+    };
+    if (PERSIST) {
+        for (;;) {
+            int it0 = 0;
+            if (lane == 0) it0 = atomicAdd(a.queue, PERSIST_CHUNK);
+            it0 = __builtin_amdgcn_readfirstlane(it0);
+            if ((int64_t)it0 >= units) break;
+            const int64_t end = (int64_t)it0 + PERSIST_CHUNK < units ? (int64_t)it0 + PERSIST_CHUNK : units;
+            for (int64_t w = it0; w < end; ++w) unit(w);
+        }
+    } else {
+        const int64_t nb = (units + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK;
+        for (int64_t blk = xcd_block(blockIdx.x, gridDim.x, a.n_xcd, XCD_RUN_LINES); blk < nb; blk += gridDim.x) {
+            const int64_t w = blk * WAVES_PER_BLOCK + uni(threadIdx.x >> 6);
+            if (w < units) unit(w);
+        }
+    }
+}
+
+// Padded copies of the tables (see sweep_lines): row p holds, block after block, V copies of the
+// block's first value, its values, V copies of its last.
+template <typename T>
+__global__ __launch_bounds__(256) void k_pad_tables(const SolveLaunch a, int V, T* __restrict__ pc, T* __restrict__ pe) {
+    const T* __restrict__ chi = (const T*)a.chi;
+    const T* __restrict__ eta = (const T*)a.eta;
+    const int64_t n = a.P * a.pad_ld;
+    for (int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x; i < n; i += (int64_t)gridDim.x * blockDim.x) {
+        const int64_t p = i / a.pad_ld;
+        int c = (int)(i - p * a.pad_ld), f = a.F - 1;
+#pragma unroll
+        for (int b = 0; b < RT_MAX_FREQ_BLOCKS; ++b)
+            if (b < a.n_blocks && c >= 0) {
+                const int L = a.blk_start[b + 1] - a.blk_start[b];
+                const int j = c - V;
+                if (c < L + 2 * V) f = a.blk_start[b] + (j < 0 ? 0 : j >= L ? L - 1 : j);
+                c -= L + 2 * V;
+            }
+        pc[i] = chi[p * a.ld + f];
+        pe[i] = eta[p * a.ld + f];
     }
 }
 
@@ -1287,10 +1724,92 @@ static void solve_dispatch(const SolveLaunch& a, bool persist, dim3 grid, hipStr
     }
 }
 
+// Values per lane of the multi-line sweep for this launch's frequencies, lanes per line, lines per wave and
+// chunks of 64 lanes per line; false when it does not apply.
+bool plan_lines(SolveLaunch& a, int precision) {
+    a.vpl = 0;
+    if (a.scheme != RT_SCHEME_FEAUTRIER2 || a.dtau_max_rcp > 0.0 || a.dv_max_rcp > 0.0) return false;
+    const bool moving = a.vel != nullptr;
+    const size_t es = precision == RT_F64 ? 8 : 4;
+    double best = 0.0;
+    for (int V : {4, 3, 2}) {
+        if ((V == 2) != (precision == RT_F64)) continue;
+        int lanes = 0, ld = 0;
+        if (moving) {
+            for (int b = 0; b < a.n_blocks; ++b) {
+                const int L = a.blk_start[b + 1] - a.blk_start[b];
+                lanes += (L + V - 1) / V;
+                ld += L + 2 * V;
+            }
+            if ((double)a.P * ld * es >= 4294967296.0) continue;  // 32-bit row offsets
+        } else {
+            if (a.F < V || !a.small_tables) continue;
+            lanes = (a.F + V - 1) / V;
+        }
+        const int lpl = lanes < 64 ? lanes : 64;
+        // a moving line's chunk repeats the neighbouring chunks' lanes on both sides (line_lane)
+        const int chunks = lanes <= 64 ? 1 : moving ? (lanes + 61) / 62 : (lanes + 63) / 64;
+        // frequencies per wave instruction, against V frequencies' work plus what a point costs by itself
+        // (about 15 and 14 instructions)
+        const int lines = 64 / lpl < 16 ? 64 / lpl : 16;
+        const double rate = (double)a.F * lines / chunks / (15.0 * V + 14.0);
+        if (rate > best) {
+            best = rate;
+            a.vpl = V;
+            a.lpl = lpl;
+            a.lines = lines;
+            a.line_chunks = chunks;
+            a.pad_ld = ld;
+        }
+    }
+    return a.vpl != 0;
+}
+
+size_t pad_table_bytes(const SolveLaunch& a, int precision) {  // of one table (a few values read past the last row's end)
+    return ((size_t)a.P * a.pad_ld + 8) * (precision == RT_F64 ? 8 : 4);
+}
+
+hipError_t launch_pad(const SolveLaunch& a, int precision, hipStream_t s) {
+    const unsigned g = capped_blocks((a.P * a.pad_ld + 255) / 256);
+    if (precision == RT_F64)
+        hipLaunchKernelGGL(k_pad_tables<double>, dim3(g), dim3(256), 0, s, a, a.vpl, (double*)a.pad_chi,
+                           (double*)a.pad_eta);
+    else
+        hipLaunchKernelGGL(k_pad_tables<float>, dim3(g), dim3(256), 0, s, a, a.vpl, (float*)a.pad_chi,
+                           (float*)a.pad_eta);
+    return hipGetLastError();
+}
+
+template <typename T, int V, bool PERSIST>
+static void lines_dispatch(const SolveLaunch& a, dim3 grid, hipStream_t s) {
+    bool udx = true;
+    for (int b = 1; b < a.n_blocks; ++b) udx = udx && (a.inv_dx[b] == a.inv_dx[0]);
+#define RT_LAUNCH(MV, U) hipLaunchKernelGGL((k_solve_lines<T, V, MV, U, PERSIST>), grid, dim3(SOLVE_BLOCK), 0, s, a)
+    if (a.vel && udx) RT_LAUNCH(true, true);
+    else if (a.vel) RT_LAUNCH(true, false);
+    else RT_LAUNCH(false, true);
+#undef RT_LAUNCH
+}
+
 hipError_t launch_solve(const SolveLaunch& a, int precision, hipStream_t s) {
     const int64_t n_items = solve_items(a);
     if (n_items == 0) return hipSuccess;
     const bool persist = a.schedule == RT_SCHED_BINNED;
+    if (a.vpl && (!a.vel || a.pad_chi)) {  // several lines per wave
+        const int64_t units = (a.n_origins * a.R + a.lines - 1) / a.lines * a.line_chunks;
+        const dim3 lg = persist ? dim3((unsigned)((a.grid_waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK))
+                                : dim3(capped_blocks((units + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK));
+#define RT_LINES(T, V)                                                 \
+    do {                                                               \
+        if (persist) lines_dispatch<T, V, true>(a, lg, s);             \
+        else lines_dispatch<T, V, false>(a, lg, s);                    \
+    } while (0)
+        if (precision == RT_F64) RT_LINES(double, 2);
+        else if (a.vpl == 3) RT_LINES(float, 3);
+        else RT_LINES(float, 4);
+#undef RT_LINES
+        return hipGetLastError();
+    }
     dim3 grid = persist ? dim3((unsigned)((a.grid_waves + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK))
                         : dim3(capped_blocks((n_items + WAVES_PER_BLOCK - 1) / WAVES_PER_BLOCK));
     if (precision == RT_F64) solve_dispatch<double>(a, persist, grid, s);
