@@ -15,8 +15,8 @@
 // accumulate in FP32 (MFMA); biases and the head are FP32; the backward signal
 // dz = dh * silu'(z) is rounded to BF16 before it enters the matrix cores.
 //
-// Tiles: forward, one workgroup (4 waves) takes 64 or 128 samples, each wave
-// owning 64 of the 256 output columns (v_mfma_f32_16x16x16_bf16), activations
+// Tiles: forward, one workgroup (8 waves) takes 32 or 64 samples, each wave
+// owning 32 of the 256 output columns (v_mfma_f32_16x16x16_bf16), activations
 // kept in LDS between layers; for many samples a persistent kernel holds the
 // hidden weights in registers (v_mfma_f32_16x16x32_bf16).  Backward: a signal
 // pass per 32-sample tile and a split-K weight pass over sample chunks, both on
@@ -57,13 +57,26 @@ constexpr int64_t MAX_SAMPLES = ((int64_t)1 << 31) - 1;  // sample indices are i
 
 // BF16 copies: forward (transposed [N][K]) and backward ([K][N]) layouts
 constexpr int64_t WT1 = 0;                 // [256][16]
-constexpr int64_t WT2 = WT1 + HW * DIN;    // [256][256]
-constexpr int64_t WT3 = WT2 + HW * HW;     // [256][256]
+constexpr int64_t WT2 = WT1 + HW * DIN;    // [256][256] in fragment order (frag_t)
+constexpr int64_t WT3 = WT2 + HW * HW;     // likewise
 constexpr int64_t WT4 = WT3 + HW * HW;     // [16][256], rows >= 2 zero
 constexpr int64_t NWT = WT4 + 16 * HW;
-constexpr int64_t WB2 = 0;                 // [256][256]
+constexpr int64_t WB2 = 0;                 // [256][256] in fragment order (frag_b)
 constexpr int64_t WB3 = WB2 + HW * HW;
 constexpr int64_t NWB = WB3 + HW * HW;
+
+// The hidden layers' copies are stored in the order in which a wave's lanes take them as matrix
+// operands, so that a fragment load is 64 consecutive 16-byte pieces; in rows, each load touched 16
+// rows and each line was fetched by several of them (forward of 8192 samples 21 us, one workgroup's
+// stream of weights).  frag_t: Wt[n][k] for two k-steps of 16 (lane 16 g + r: row n = r of its 16,
+// columns 4g .. 4g+3 of either step).  frag_b: W[j][n] for a k-step of 32 (lane 16 g + r: row j = r,
+// columns 8g .. 8g+7).
+__host__ __device__ inline int frag_t(int n, int k) {
+    return ((n >> 4) * 8 + (k >> 5)) * 512 + (((k >> 2) & 3) * 16 + (n & 15)) * 8 + ((k >> 4) & 1) * 4 + (k & 3);
+}
+__host__ __device__ inline int frag_b(int j, int n) {
+    return ((j >> 4) * 8 + (n >> 5)) * 512 + (((n >> 3) & 3) * 16 + (j & 15)) * 8 + (n & 7);
+}
 
 typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
 typedef float f32x2 __attribute__((ext_vector_type(2)));
@@ -111,11 +124,12 @@ __global__ void k_publish(const float* __restrict__ w, uint16_t* __restrict__ wt
         wt[WT1 + i] = f2bf(w[OFF_W1 + (int64_t)k * HW + n]);
     }
     if (i < HW * HW) {
-        const int n = (int)(i / HW), k = (int)(i % HW);
-        wt[WT2 + i] = f2bf(w[OFF_W2 + (int64_t)k * HW + n]);
-        wt[WT3 + i] = f2bf(w[OFF_W3 + (int64_t)k * HW + n]);
-        wb[WB2 + i] = f2bf(w[OFF_W2 + i]);
-        wb[WB3 + i] = f2bf(w[OFF_W3 + i]);
+        const int k = (int)(i / HW), n = (int)(i % HW);
+        const uint16_t h2 = f2bf(w[OFF_W2 + i]), h3 = f2bf(w[OFF_W3 + i]);
+        wt[WT2 + frag_t(n, k)] = h2;
+        wt[WT3 + frag_t(n, k)] = h3;
+        wb[WB2 + frag_b(k, n)] = h2;
+        wb[WB3 + frag_b(k, n)] = h3;
     }
     if (i < 16 * HW) {  // W4t[c][k] = W4[k][c], c < 2
         const int c = (int)(i / HW), k = (int)(i % HW);
@@ -125,39 +139,59 @@ __global__ void k_publish(const float* __restrict__ w, uint16_t* __restrict__ wt
 
 // ---------------------------------------------------------------- forward
 
+// The wave's A operands of a hidden layer's Wt (columns [32w, 32w+32) of the layer), all k-steps,
+// loaded ahead of the product that uses them.
+typedef short v8i16 __attribute__((ext_vector_type(8)));
+__device__ inline v8i16 ld8(const uint16_t* p) { return *(const v8i16*)p; }  // 16-byte aligned
+__device__ __attribute__((always_inline)) inline void fwd_load_w(const uint16_t* __restrict__ Wt,
+                                                                 v4i16 (&wf)[HW / 16][2]) {
+    const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
+#pragma unroll
+    for (int ks = 0; ks < HW / 32; ++ks)
+#pragma unroll
+        for (int nt = 0; nt < 2; ++nt) {
+            const v8i16 v = ld8(Wt + ((2 * w + nt) * 8 + ks) * 512 + 8 * lane);
+            wf[2 * ks][nt] = __builtin_shufflevector(v, v, 0, 1, 2, 3);
+            wf[2 * ks + 1][nt] = __builtin_shufflevector(v, v, 4, 5, 6, 7);
+        }
+}
+
 // out[m][n] = bf16(silu(z)), z = bf16(b[n] + sum_k in[m][k] W[k][n]) for the
-// 16*MTW samples m of the tile, W given as Wt[256][K].  The product is formed
+// 16*MTW samples m of the tile, W's fragments in wf.  The product is formed
 // transposed (Z^T = Wt in^T: weights as the A operand, samples as B) so that a
 // lane's four accumulators are four consecutive n of one sample and go out as
-// one 8-byte store; they start from the bias.  Wave w owns n in [64w, 64w+64).
-template <int MTW, int K, int ldin, bool KEEP>
-__device__ __attribute__((always_inline)) inline void fwd_layer(const uint16_t* in, const uint16_t* __restrict__ Wt,
-                                                                const float* __restrict__ bias, uint16_t* out,
+// one 8-byte store; they start from the bias.  Wave w owns n in [32w, 32w+32).
+// Once the products are issued, wf is refilled from Wnext (if given).
+template <int MTW, int KS, int ldin, bool KEEP>
+__device__ __attribute__((always_inline)) inline void fwd_layer(const uint16_t* in, v4i16 (&wf)[KS][2],
+                                                                const float* __restrict__ bias,
+                                                                const uint16_t* __restrict__ Wnext, uint16_t* out,
                                                                 uint16_t* __restrict__ zout, int64_t row0,
                                                                 int nvalid) {
     const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
     const int g = lane >> 4, r = lane & 15;
-    v4f32 acc[4][MTW];
+    v4f32 acc[2][MTW];
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const float4 bb = *(const float4*)(bias + 64 * w + 16 * nt + 4 * g);
+    for (int nt = 0; nt < 2; ++nt) {
+        const float4 bb = *(const float4*)(bias + 32 * w + 16 * nt + 4 * g);
 #pragma unroll
         for (int mt = 0; mt < MTW; ++mt) acc[nt][mt] = (v4f32){bb.x, bb.y, bb.z, bb.w};
     }
-    for (int k0 = 0; k0 < K; k0 += 16) {
-        v4i16 a[4], b[MTW];
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt) a[nt] = ld4(Wt + (int64_t)(64 * w + 16 * nt + r) * K + k0 + 4 * g);
+    for (int ks = 0; ks < KS; ++ks) {
+        v4i16 b[MTW];
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) b[mt] = ld4(in + (mt * 16 + r) * ldin + k0 + 4 * g);
+        for (int mt = 0; mt < MTW; ++mt) b[mt] = ld4(in + (mt * 16 + r) * ldin + 16 * ks + 4 * g);
 #pragma unroll
-        for (int nt = 0; nt < 4; ++nt)
+        for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
-            for (int mt = 0; mt < MTW; ++mt) acc[nt][mt] = mfma(a[nt], b[mt], acc[nt][mt]);
+            for (int mt = 0; mt < MTW; ++mt) acc[nt][mt] = mfma(wf[ks][nt], b[mt], acc[nt][mt]);
     }
+    if constexpr (KS > 1)
+        if (Wnext) fwd_load_w(Wnext, wf);
 #pragma unroll
-    for (int nt = 0; nt < 4; ++nt) {
-        const int n0 = 64 * w + 16 * nt + 4 * g;
+    for (int nt = 0; nt < 2; ++nt) {
+        const int n0 = 32 * w + 16 * nt + 4 * g;
 #pragma unroll
         for (int mt = 0; mt < MTW; ++mt) {
             const int m = mt * 16 + r;
@@ -171,50 +205,114 @@ __device__ __attribute__((always_inline)) inline void fwd_layer(const uint16_t* 
     }
 }
 
+// mean Gaussian NLL of one of n samples, 0.5 (exp(-s) (t - m)^2 + s), and dY for the mean
+__device__ inline float nll_one(float m, float s, float t, int64_t n, float2& dy) {
+    const float e = __expf(-s), d = t - m;
+    dy = make_float2(-(e * d) / (float)n, 0.5f * (1.f - e * d * d) / (float)n);
+    return 0.5f * (e * d * d + s);
+}
+
+// Row i of training step k: drawn from (seed, k).
+__device__ inline int32_t train_row(uint64_t seed, uint64_t k, uint64_t batch, uint64_t i, uint64_t N) {
+    uint64_t z = seed + (k * batch + i + 1) * 0x9E3779B97F4A7C15ull;
+    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
+    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
+    z ^= z >> 31;
+    return (int32_t)(z % N);
+}
+
+// What the forward of a training step does besides: draw the rows, form the loss and dY.
+struct FwdTrain {
+    const int64_t* st;  // step number
+    uint64_t seed;
+    int64_t N;
+    const float* T;     // targets [N]
+    int32_t* rows;      // drawn rows [n], for the backward
+    float* dY;          // [n][2]
+    float* loss;        // sums of 16 samples' losses [ceil(n / 16)], by whole tiles
+};
+
 // Forward over tiles of 16*MTW samples (rows[i] selects the input row of
-// sample i when given); KEEP stores the BF16 pre-activations Z[3][n][256].
-template <bool KEEP, int MTW>
-__global__ __launch_bounds__(256, MTW == 4 ? 2 : 1) void k_mlp_fwd(
-    const uint16_t* __restrict__ wt, const float* __restrict__ w, const uint16_t* __restrict__ X,
-    const int32_t* __restrict__ rows, int64_t n, float* __restrict__ Y, uint16_t* __restrict__ Z) {
+// sample i when given); KEEP stores the BF16 pre-activations Z[3][n][256];
+// TRAIN draws the rows and writes dY.
+//
+// A small batch is a chain of latencies: inputs, three layers with a barrier
+// each, the head.  Eight waves hold a layer's weights in registers, loaded
+// during the layer before, and tiles are 32 samples so that a batch of 8192
+// covers all 256 CUs.  Measured with pre-activations kept: 8192 samples 25.6 ->
+// 12.3 us (four waves on 64-sample tiles, weights loaded inside the products ->
+// this), 100 samples 23.2 -> 9.4, 65535 83.5 -> 51.7.  Eight waves alone, with
+// the weights still in rows: 22.1 us.
+template <bool KEEP, int MTW, bool TRAIN>
+__global__ __launch_bounds__(512, MTW == 2 ? 4 : 2) void k_mlp_fwd(const uint16_t* __restrict__ wt, const float* __restrict__ w,
+                                                    const uint16_t* __restrict__ X, const int32_t* __restrict__ rows,
+                                                    int64_t n, float* __restrict__ Y, uint16_t* __restrict__ Z,
+                                                    const FwdTrain tr) {
     constexpr int TS = 16 * MTW;
     __shared__ __attribute__((aligned(16))) uint16_t sx[TS * LDX];
     __shared__ __attribute__((aligned(16))) uint16_t sa[TS * LDH];
     __shared__ __attribute__((aligned(16))) uint16_t sb[TS * LDH];
+    __shared__ float st[TRAIN ? TS : 1];  // targets
     const int64_t row0 = (int64_t)blockIdx.x * TS;
     const int nvalid = (int)(n - row0 < TS ? n - row0 : TS);
-    for (int t = threadIdx.x; t < TS * 4; t += 256) {  // TS x 16 inputs, 4 per thread
-        const int m = t >> 2, q = t & 3;
+    v4i16 w1[1][2], wf[HW / 16][2];
+    if (threadIdx.x < TS * 4) {  // TS x 16 inputs, 4 per thread
+        const int t = threadIdx.x, m = t >> 2, q = t & 3;
         v4i16 v = (v4i16){0, 0, 0, 0};
         if (m < nvalid) {
-            const int64_t src = rows ? (int64_t)rows[row0 + m] : row0 + m;
+            int64_t src = row0 + m;
+            if (TRAIN) {
+                src = train_row(tr.seed, (uint64_t)*tr.st, (uint64_t)n, (uint64_t)src, (uint64_t)tr.N);
+                if (q == 0) {
+                    tr.rows[row0 + m] = (int32_t)src;
+                    st[m] = tr.T[src];
+                }
+            } else if (rows) {
+                src = rows[src];
+            }
             v = ld4(X + src * DIN + 4 * q);
         }
         *(v4i16*)(sx + m * LDX + 4 * q) = v;
     }
+    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
+    const int g = lane >> 4, r = lane & 15;
+    for (int nt = 0; nt < 2; ++nt) w1[0][nt] = ld4(wt + WT1 + (32 * wv + 16 * nt + r) * DIN + 4 * g);
+    fwd_load_w(wt + WT2, wf);
     __syncthreads();
     uint16_t* Z1 = KEEP ? Z : nullptr;
     uint16_t* Z2 = KEEP ? Z + n * HW : nullptr;
     uint16_t* Z3 = KEEP ? Z + 2 * n * HW : nullptr;
-    fwd_layer<MTW, DIN, LDX, KEEP>(sx, wt + WT1, w + OFF_B1, sa, Z1, row0, nvalid);
+    fwd_layer<MTW, 1, LDX, KEEP>(sx, w1, w + OFF_B1, nullptr, sa, Z1, row0, nvalid);
     __syncthreads();
-    fwd_layer<MTW, HW, LDH, KEEP>(sa, wt + WT2, w + OFF_B2, sb, Z2, row0, nvalid);
+    fwd_layer<MTW, HW / 16, LDH, KEEP>(sa, wf, w + OFF_B2, wt + WT3, sb, Z2, row0, nvalid);
     __syncthreads();
-    fwd_layer<MTW, HW, LDH, KEEP>(sb, wt + WT3, w + OFF_B3, sa, Z3, row0, nvalid);
+    fwd_layer<MTW, HW / 16, LDH, KEEP>(sb, wf, w + OFF_B3, nullptr, sa, Z3, row0, nvalid);
     __syncthreads();
-    // head, transposed as the hidden layers: wave w takes the 16-sample groups
-    // w, w+4, ...; the A operand is W4t (rows 0 and 1 used), so lanes with
-    // g = 0 hold y[m][0..1]
-    const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int g = lane >> 4, r = lane & 15;
-    for (int grp = wv; grp < MTW; grp += 4) {
+    // head, transposed as the hidden layers: wave w takes the 16-sample group
+    // w; the A operand is W4t (rows 0 and 1 used), so lanes with g = 0 hold
+    // y[m][0..1]
+    if (wv < MTW) {
         v4f32 acc = (v4f32){0.f, 0.f, 0.f, 0.f};
+#pragma unroll
         for (int k0 = 0; k0 < HW; k0 += 16)
-            acc = mfma(ld4(wt + WT4 + (int64_t)r * HW + k0 + 4 * g), ld4(sa + (16 * grp + r) * LDH + k0 + 4 * g),
-                       acc);
-        const int m = 16 * grp + r;
-        if (g == 0 && m < nvalid)
-            *(float2*)(Y + (row0 + m) * DOUT) = make_float2(acc[0] + w[OFF_B4], acc[1] + w[OFF_B4 + 1]);
+            acc = mfma(r < DOUT ? ld4(wt + WT4 + r * HW + k0 + 4 * g) : (v4i16){0, 0, 0, 0},
+                       ld4(sa + (16 * wv + r) * LDH + k0 + 4 * g), acc);
+        const int m = 16 * wv + r;
+        float l = 0.f;
+        if (g == 0 && m < nvalid) {
+            const float2 y = make_float2(acc[0] + w[OFF_B4], acc[1] + w[OFF_B4 + 1]);
+            if (TRAIN) {
+                float2 dy;
+                l = nll_one(y.x, y.y, st[m], n, dy);
+                *(float2*)(tr.dY + (row0 + m) * DOUT) = dy;
+            } else {
+                *(float2*)(Y + (row0 + m) * DOUT) = y;
+            }
+        }
+        if (TRAIN) {
+            for (int o = 8; o > 0; o >>= 1) l += __shfl_xor(l, o, 64);
+            if (lane == 0) tr.loss[row0 / 16 + wv] = l;
+        }
     }
 }
 
@@ -233,7 +331,6 @@ __global__ __launch_bounds__(256, MTW == 4 ? 2 : 1) void k_mlp_fwd(
 // weights from LDS.  Rounding points and results are those of k_mlp_fwd (the
 // products are summed 32 at a time instead of 16, so a BF16 rounding of z may
 // fall the other way).
-typedef short v8i16 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16x8 __attribute__((ext_vector_type(8)));
 constexpr int PT = 64;          // samples per tile
 constexpr int PWAVES = 8;       // waves per workgroup
@@ -246,7 +343,6 @@ __device__ inline v4f32 mfma32(v8i16 a, v8i16 b, v4f32 c) {
     return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16x8, a), __builtin_bit_cast(bf16x8, b), c,
                                                    0, 0, 0);
 }
-__device__ inline v8i16 ld8(const uint16_t* p) { return *(const v8i16*)p; }  // 16-byte aligned
 
 // Each tile is taken in two halves of 32 samples, A and B, one half behind
 // the other: while a wave's matrix products of one half run, its epilogue
@@ -374,9 +470,9 @@ __global__ __launch_bounds__(512, 1) void k_mlp_fwd_ws(const uint16_t* __restric
     for (int nt = 0; nt < 2; ++nt)
 #pragma unroll
         for (int ks = 0; ks < 8; ++ks) {
-            const int64_t o = (int64_t)(32 * wv + 16 * nt + r) * HW + 32 * ks + 8 * g;
-            w2r[nt][ks] = ld8(wt + WT2 + o);
-            w3r[nt][ks] = ld8(wt + WT3 + o);
+            const int o = frag_t(32 * wv + 16 * nt + r, 32 * ks + 8 * g), o4 = o + 16 * 8;  // columns 8g .. +3, +4 .. +7
+            w2r[nt][ks] = __builtin_shufflevector(ld4(wt + WT2 + o), ld4(wt + WT2 + o4), 0, 1, 2, 3, 4, 5, 6, 7);
+            w3r[nt][ks] = __builtin_shufflevector(ld4(wt + WT3 + o), ld4(wt + WT3 + o4), 0, 1, 2, 3, 4, 5, 6, 7);
         }
     const float b40 = w[OFF_B4], b41 = w[OFF_B4 + 1];
     const int64_t tiles = (n + PT - 1) / PT;
@@ -509,11 +605,10 @@ __device__ inline void bwd_store_ht(const uint16_t* sz, uint16_t* __restrict__ H
 __device__ __attribute__((always_inline)) inline void bwd_load_w(const uint16_t* __restrict__ Wb,
                                                                  v8i16 (&wf)[8][2]) {
     const int lane = threadIdx.x & 63, wv = threadIdx.x >> 6;
-    const int g = lane >> 4, r = lane & 15;
 #pragma unroll
     for (int ks = 0; ks < 8; ++ks)
 #pragma unroll
-        for (int nt = 0; nt < 2; ++nt) wf[ks][nt] = ld8(Wb + (int64_t)(32 * wv + 16 * nt + r) * HW + 32 * ks + 8 * g);
+        for (int nt = 0; nt < 2; ++nt) wf[ks][nt] = ld8(Wb + ((2 * wv + nt) * 8 + ks) * 512 + 8 * lane);
 }
 
 // dZ_prev[m][j] = bf16((sum_n dZ[m][n] W[j][n]) silu'(z[m][j])) for the tile: dZ in sd
@@ -541,7 +636,7 @@ __device__ __attribute__((always_inline)) inline void bwd_signal_layer(uint16_t*
 #pragma unroll
             for (int nt = 0; nt < 2; ++nt) acc[mt][nt] = mfma32(a[mt], wf[ks][nt], acc[mt][nt]);
     }
-    bwd_load_w(Wnext, wf);
+    if (Wnext) bwd_load_w(Wnext, wf);
     __syncthreads();  // every wave has read dZ before it is replaced
 #pragma unroll
     for (int mt = 0; mt < 2; ++mt)
@@ -568,13 +663,15 @@ __global__ __launch_bounds__(SIG_THREADS, 1) void k_bwd_signal(const uint16_t* _
                                                                const int32_t* __restrict__ rows, int64_t n,
                                                                int64_t npad, const uint16_t* __restrict__ Z,
                                                                const float* __restrict__ dY, uint16_t* __restrict__ T,
-                                                               uint16_t* __restrict__ XT, float* __restrict__ sp) {
+                                                               uint16_t* __restrict__ XT, float* __restrict__ sp,
+                                                               int n_xcd) {
     __shared__ __attribute__((aligned(16))) uint16_t sd[BT * LDH];  // dZ of the current layer, [m][j]
     __shared__ __attribute__((aligned(16))) uint16_t sz[BT * LDH];  // z of the layer below, [m][j]
     __shared__ float sdy[BT * DOUT];
     __shared__ float sred[6 * HW];  // the second half's column partials, added in a fixed order
     const int t = threadIdx.x, j = t & (HW - 1), hs = t / HW;
     const int64_t tiles = npad / BT, plane = HW * npad;
+    const int64_t group = xcd_block(blockIdx.x, gridDim.x, n_xcd, 2);  // two tiles share a line of T
     const uint16_t* Z1 = Z;
     const uint16_t* Z2 = Z + n * HW;
     const uint16_t* Z3 = Z + 2 * n * HW;
@@ -587,7 +684,7 @@ __global__ __launch_bounds__(SIG_THREADS, 1) void k_bwd_signal(const uint16_t* _
     float gw0 = 0.f, gw1 = 0.f, gb3 = 0.f, gb2 = 0.f, gb1 = 0.f, gb4 = 0.f;  // partials of column j, half hs
     v8i16 wf[8][2];
     bwd_load_w(wb + WB3, wf);
-    for (int64_t tile = blockIdx.x; tile < tiles; tile += gridDim.x) {
+    for (int64_t tile = group; tile < tiles; tile += gridDim.x) {
         const int64_t row0 = tile * BT;
         const int nvalid = (int)(n - row0 < BT ? n - row0 : BT);
         if (t < BT * DOUT) {
@@ -649,7 +746,7 @@ __global__ __launch_bounds__(SIG_THREADS, 1) void k_bwd_signal(const uint16_t* _
         bwd_put_z(z1, sz);
         __syncthreads();
         bwd_store_ht(sz, HT1, npad, row0, nvalid, j, hs);
-        bwd_signal_layer(sd, sz, wf, wb + WB3, dZT1, npad, row0, nvalid);  // W3 again for the next tile
+        bwd_signal_layer(sd, sz, wf, tile + gridDim.x < tiles ? wb + WB3 : nullptr, dZT1, npad, row0, nvalid);
         __syncthreads();
         for (int m = SIG_HALF * hs; m < SIG_HALF * (hs + 1); ++m) gb1 += bf2f(sd[m * LDH + j]);
         __syncthreads();  // before the next tile overwrites sd, sz, sdy
@@ -664,7 +761,7 @@ __global__ __launch_bounds__(SIG_THREADS, 1) void k_bwd_signal(const uint16_t* _
     }
     __syncthreads();
     if (hs == 0) {
-        float* part = sp + blockIdx.x * (int64_t)SMALLP;
+        float* part = sp + group * SMALLP;
         part[SP_W4 + j * DOUT] = gw0 + sred[0 * HW + j];
         part[SP_W4 + j * DOUT + 1] = gw1 + sred[1 * HW + j];
         part[SP_B3 + j] = gb3 + sred[2 * HW + j];
@@ -735,6 +832,44 @@ __device__ __attribute__((always_inline)) inline void wgrad_block(const uint16_t
     }
 }
 
+// bias correction 1 - b^t, formed in FP64 and rounded once (host and device agree)
+__host__ __device__ inline float bias_corr(float b, int64_t t) { return (float)(1.0 - pow((double)b, (double)t)); }
+
+// What the last workgroup of a training step's weight pass does (st null: no training step).
+struct StepScalars {
+    int64_t* st;         // step number; the floats after it: learning rate, bias corrections
+    const float* loss;   // partial sums of the step's loss (null: already added), how many, where to
+    int64_t n_loss;
+    float* loss_sum;     // may be null
+    rt_train_opts o;
+};
+
+// The scalars of step k = *st (cosine learning rate, bias corrections of k + 1), then k += 1; the
+// step's loss, summed in a fixed order and added once.
+__device__ inline void step_scalars(const StepScalars& q, float* red) {
+    const int t = threadIdx.x;
+    if (q.loss && q.loss_sum) {
+        float l = 0.f;
+        for (int64_t i = t; i < q.n_loss; i += 256) l += q.loss[i];
+        red[t] = l;
+        __syncthreads();
+        for (int h = 128; h > 0; h >>= 1) {
+            if (t < h) red[t] += red[t + h];
+            __syncthreads();
+        }
+        if (t == 0) *q.loss_sum += red[0];
+    }
+    if (t != 0) return;
+    const rt_train_opts& o = q.o;
+    const int64_t k = *q.st;
+    const double frac = (double)(k < o.total_steps ? k : o.total_steps) / (double)o.total_steps;
+    float* c = (float*)(q.st + 1);
+    c[0] = (float)((double)o.lr_final + 0.5 * ((double)o.lr - (double)o.lr_final) * (1.0 + cos(3.141592653589793 * frac)));
+    c[1] = bias_corr(o.b1, k + 1);
+    c[2] = bias_corr(o.b2, k + 1);
+    *q.st = k + 1;
+}
+
 // Weight pass: workgroup b takes chunk b % n_chunks of job b / n_chunks; jobs 0..15 are the
 // 64 x 64 blocks of W3 (H2^T dZ3), 16..31 those of W2 (H1^T dZ2), 32..35 the
 // 16 x 64 blocks of W1 (X^T dZ1), and jobs 36.. add the chunk's share of the signal pass's
@@ -742,8 +877,12 @@ __device__ __attribute__((always_inline)) inline void wgrad_block(const uint16_t
 // chunk's partials.
 __global__ __launch_bounds__(256) void k_bwd_wgrad(const uint16_t* __restrict__ T, const uint16_t* __restrict__ XT,
                                                     int64_t npad, int n_chunks, const float* __restrict__ sp,
-                                                    int n_groups, float* __restrict__ bp) {
+                                                    int n_groups, float* __restrict__ bp, const StepScalars step) {
     __shared__ __attribute__((aligned(16))) float red[4 * 4 * 4 * 4 * 64];
+    if (blockIdx.x == (unsigned)(WG_JOBS * n_chunks)) {  // a training step's last workgroup: its scalars
+        step_scalars(step, red);
+        return;
+    }
     const int64_t plane = HW * npad;
     const int chunk = (int)(blockIdx.x % n_chunks), job = (int)(blockIdx.x / n_chunks);
     const int64_t steps = npad / 32, per = (steps + n_chunks - 1) / n_chunks;
@@ -773,37 +912,43 @@ __global__ __launch_bounds__(256) void k_bwd_wgrad(const uint16_t* __restrict__ 
     }
 }
 
-// grad[p] += the chunk partials of p, in chunk order
-__global__ void k_grad_sum(const float* __restrict__ bp, int n_chunks, float* __restrict__ grad) {
-    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (p >= NPARAM) return;
-    int64_t src;
-    if (p < OFF_B1) src = BP_W1 + (p - OFF_W1);
-    else if (p < OFF_W2) src = BP_SMALL + SP_B1 + (p - OFF_B1);
-    else if (p < OFF_B2) src = BP_W2 + (p - OFF_W2);
-    else if (p < OFF_W3) src = BP_SMALL + SP_B2 + (p - OFF_B2);
-    else if (p < OFF_B3) src = BP_W3 + (p - OFF_W3);
-    else if (p < OFF_W4) src = BP_SMALL + SP_B3 + (p - OFF_B3);
-    else if (p < OFF_B4) src = BP_SMALL + SP_W4 + (p - OFF_W4);
-    else src = BP_SMALL + SP_B4 + (p - OFF_B4);
-    float s = 0.f;
-    for (int c = 0; c < n_chunks; ++c) s += bp[(int64_t)c * NBIG + src];
-    grad[p] += s;
+// Where a chunk's partials hold parameter p.
+__device__ inline int64_t partial_of(int64_t p) {
+    if (p < OFF_B1) return BP_W1 + (p - OFF_W1);
+    if (p < OFF_W2) return BP_SMALL + SP_B1 + (p - OFF_B1);
+    if (p < OFF_B2) return BP_W2 + (p - OFF_W2);
+    if (p < OFF_W3) return BP_SMALL + SP_B2 + (p - OFF_B2);
+    if (p < OFF_B3) return BP_W3 + (p - OFF_W3);
+    if (p < OFF_W4) return BP_SMALL + SP_B3 + (p - OFF_B3);
+    if (p < OFF_B4) return BP_SMALL + SP_W4 + (p - OFF_W4);
+    return BP_SMALL + SP_B4 + (p - OFF_B4);
 }
 
-// mean Gaussian NLL: 0.5 (exp(-s) (t - m)^2 + s); dY for the mean over n samples
+// the chunk partials of p, in chunk order
+__device__ inline float partial_sum(const float* __restrict__ bp, int n_chunks, int64_t p) {
+    const float* src = bp + partial_of(p);
+    float s = 0.f;
+#pragma unroll 8
+    for (int c = 0; c < n_chunks; ++c) s += src[(int64_t)c * NBIG];
+    return s;
+}
+
+// grad[p] += the chunk partials of p
+__global__ void k_grad_sum(const float* __restrict__ bp, int n_chunks, float* __restrict__ grad) {
+    const int64_t p = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
+    if (p < NPARAM) grad[p] += partial_sum(bp, n_chunks, p);
+}
+
+// loss and dY of n samples (nll_one)
 __global__ void k_nll(const float* __restrict__ Y, const float* __restrict__ T, const int32_t* __restrict__ rows,
                       int64_t n, float* __restrict__ dY, float* __restrict__ loss_sum) {
     __shared__ float red[256];
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
     float l = 0.f;
     if (i < n) {
-        const float m = Y[2 * i], s = Y[2 * i + 1];
-        const float t = T[rows ? (int64_t)rows[i] : i];
-        const float e = __expf(-s), d = t - m;
-        l = 0.5f * (e * d * d + s);
-        dY[2 * i] = -(e * d) / (float)n;
-        dY[2 * i + 1] = 0.5f * (1.f - e * d * d) / (float)n;
+        float2 dy;
+        l = nll_one(Y[2 * i], Y[2 * i + 1], T[rows ? (int64_t)rows[i] : i], n, dy);
+        *(float2*)(dY + 2 * i) = dy;
     }
     red[threadIdx.x] = l;
     __syncthreads();
@@ -832,48 +977,77 @@ __global__ void k_adam(float* __restrict__ w, const float* __restrict__ g, float
     adam_one(w, g, m, v, i, lr, b1, b2, eps, wd, c1, c2);
 }
 
-// bias correction 1 - b^t, formed in FP64 and rounded once (host and device agree)
-__host__ __device__ inline float bias_corr(float b, int64_t t) { return (float)(1.0 - pow((double)b, (double)t)); }
-
 // ---------------------------------------------------------------- training steps on the device
 //
 // The step number k lives in device memory, so one captured step serves every
-// replay: rows drawn from (seed, k), the cosine learning rate of k, the bias
-// corrections of k + 1, then k += 1.
+// replay: rows drawn from (seed, k) and the loss (k_mlp_fwd), the backward
+// passes, in whose last launch one more workgroup forms the cosine learning
+// rate of k and the bias corrections of k + 1 and counts k on, and the update.
 __global__ void k_set_step(int64_t* __restrict__ st, int64_t v) {
     if (blockIdx.x == 0 && threadIdx.x == 0) *st = v;
-}
-
-__global__ void k_step_inc(int64_t* __restrict__ st) {
-    if (blockIdx.x == 0 && threadIdx.x == 0) *st += 1;
 }
 
 __global__ void k_train_rows(const int64_t* __restrict__ st, uint64_t seed, int64_t N, int64_t batch,
                              int32_t* __restrict__ rows) {
     const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= batch) return;
-    const uint64_t k = (uint64_t)*st;
-    uint64_t z = seed + (k * (uint64_t)batch + (uint64_t)i + 1) * 0x9E3779B97F4A7C15ull;
-    z = (z ^ (z >> 30)) * 0xBF58476D1CE4E5B9ull;
-    z = (z ^ (z >> 27)) * 0x94D049BB133111EBull;
-    z ^= z >> 31;
-    rows[i] = (int32_t)(z % (uint64_t)N);
+    if (i < batch) rows[i] = train_row(seed, (uint64_t)*st, (uint64_t)batch, (uint64_t)i, (uint64_t)N);
 }
 
-__global__ void k_zero_f32(float* __restrict__ p, int64_t n) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i < n) p[i] = 0.f;
-}
-
-__global__ void k_adam_sched(float* __restrict__ w, const float* __restrict__ g, float* __restrict__ m,
-                             float* __restrict__ v, const int64_t* __restrict__ st, rt_train_opts o) {
-    const int64_t i = blockIdx.x * (int64_t)blockDim.x + threadIdx.x;
-    if (i >= NPARAM) return;
-    const int64_t k = *st;
-    const double frac = (double)(k < o.total_steps ? k : o.total_steps) / (double)o.total_steps;
-    const float lr = (float)((double)o.lr_final +
-                             0.5 * ((double)o.lr - (double)o.lr_final) * (1.0 + cos(3.141592653589793 * frac)));
-    adam_one(w, g, m, v, i, lr, o.b1, o.b2, o.eps, o.wd, bias_corr(o.b1, k + 1), bias_corr(o.b2, k + 1));
+// The update of one training step in one launch: the gradient from its chunk
+// partials, Adam, the BF16 copies.  A workgroup takes a 16 x 16 tile of W2, W3
+// or W1, turned through LDS for the transposed copy, or 256 of the remaining
+// parameters.  As separate launches (clear, sum, Adam, publish, count) these
+// cost 4 to 5 us each, next to nothing of it work; this one takes 4.6 us.  A
+// step of 8192 samples: 98 us in ten launches -> 64 us in four (forward 13.3,
+// signal pass 20.4, weight pass 15.8, update 4.6, the rest between launches).
+constexpr int STEP_TILES = 2 * (HW / 16) * (HW / 16) + HW / 16;
+constexpr int STEP_REST = 3 * HW + HW * DOUT + DOUT;  // b1, b2, b3, W4, b4
+__global__ __launch_bounds__(256) void k_train_step(const float* __restrict__ bp, int n_chunks, float* __restrict__ w,
+                                                    float* __restrict__ grad, float* __restrict__ m,
+                                                    float* __restrict__ v, uint16_t* __restrict__ wt,
+                                                    uint16_t* __restrict__ wb, const int64_t* __restrict__ st,
+                                                    const rt_train_opts o) {
+    __shared__ uint16_t tile[16][17];
+    const int t = threadIdx.x, b = blockIdx.x, ti = t >> 4, tj = t & 15;
+    constexpr int NT = HW / 16;
+    int64_t p, k0 = 0, n0 = 0;
+    int64_t copy_t = 0, copy_b = -1;  // where the tile's copies start
+    const bool tiled = b < STEP_TILES;
+    if (tiled) {
+        int q = b;
+        if (q < NT * NT) {
+            copy_t = WT2, copy_b = WB2, p = OFF_W2;
+        } else if (q < 2 * NT * NT) {
+            q -= NT * NT;
+            copy_t = WT3, copy_b = WB3, p = OFF_W3;
+        } else {
+            q -= 2 * NT * NT;
+            copy_t = WT1, p = OFF_W1;
+        }
+        k0 = q / NT * 16, n0 = q % NT * 16;
+        p += (k0 + ti) * HW + n0 + tj;
+    } else {
+        const int i = (b - STEP_TILES) * 256 + t;
+        if (i >= STEP_REST) return;
+        p = i < HW ? OFF_B1 + i : i < 2 * HW ? OFF_B2 + (i - HW) : OFF_B3 + (i - 2 * HW);  // b3, W4, b4 follow one another
+    }
+    const float* c = (const float*)(st + 1);  // learning rate, bias corrections
+    grad[p] = 0.f + partial_sum(bp, n_chunks, p);
+    adam_one(w, grad, m, v, p, c[0], o.b1, o.b2, o.eps, o.wd, c[1], c[2]);
+    const uint16_t h = f2bf(w[p]);
+    if (tiled) {
+        tile[ti][tj] = h;
+        __syncthreads();
+        if (copy_b >= 0) {
+            wb[copy_b + frag_b((int)k0 + ti, (int)n0 + tj)] = h;
+            const int e = t & 3, r = (t >> 2) & 15, g = t >> 6;
+            wt[copy_t + frag_t((int)n0 + r, (int)k0 + 4 * g + e)] = tile[4 * g + e][r];
+        } else {
+            wt[copy_t + (n0 + ti) * DIN + k0 + tj] = tile[tj][ti];
+        }
+    } else if (p >= OFF_W4 && p < OFF_B4) {
+        wt[WT4 + (p - OFF_W4) % DOUT * HW + (p - OFF_W4) / DOUT] = h;
+    }
 }
 
 // ---------------------------------------------------------------- features
@@ -1202,6 +1376,28 @@ extern "C" rt_status rt_mlp_workspace(int64_t n, int32_t training, size_t* bytes
     return RT_OK;
 }
 
+// Tiles of 32 samples while that is one tile per CU at most, else of 64, which read the weights half
+// as often.  Measured in us, 32 and 64 samples per tile, pre-activations kept: 2048 samples 10.0 and
+// 13.5, 8192 12.3 and 15.3, 16384 18.9 and 17.0, 65535 58.2 and 51.6.
+static bool fwd_small(int64_t n) { return n <= 32 * (int64_t)num_cus(); }
+
+// Batches below WS_MIN_SAMPLES (Z null: pre-activations not kept).
+static void launch_fwd_small(rt_mlp* h, const uint16_t* X, const int32_t* rows, int64_t n, float* Y, uint16_t* Z,
+                             hipStream_t s) {
+    const FwdTrain none = {};
+#define RT_FWD(KEEP, MTW)                                                                                        \
+    hipLaunchKernelGGL((k_mlp_fwd<KEEP, MTW, false>), dim3(nb(n, 16 * MTW)), dim3(512), 0, s, h->wt, h->w, X, rows, \
+                       n, Y, Z, none)
+    if (fwd_small(n)) {
+        if (Z) RT_FWD(true, 2);
+        else RT_FWD(false, 2);
+    } else {
+        if (Z) RT_FWD(true, 4);
+        else RT_FWD(false, 4);
+    }
+#undef RT_FWD
+}
+
 extern "C" rt_status rt_mlp_forward(rt_mlp* h, const uint16_t* X, const int32_t* rows, int64_t n, float* Y,
                                     int32_t keep, void* ws, size_t ws_bytes, void* stream) {
     if (!h || (n > 0 && (!X || !Y)) || n < 0 || n > MAX_SAMPLES)
@@ -1221,24 +1417,22 @@ extern "C" rt_status rt_mlp_forward(rt_mlp* h, const uint16_t* X, const int32_t*
         RT_HIP(hipGetLastError());
         return RT_OK;
     }
-    // small batches (training) in 64-sample tiles to fill the chip, large ones in 128
-    if (n < (int64_t)num_cus() * 256) {
-        if (keep)
-            hipLaunchKernelGGL((k_mlp_fwd<true, 4>), dim3(nb(n, 64)), dim3(256), 0, s, h->wt, h->w, X, rows, n, Y,
-                               (uint16_t*)ws);
-        else
-            hipLaunchKernelGGL((k_mlp_fwd<false, 4>), dim3(nb(n, 64)), dim3(256), 0, s, h->wt, h->w, X, rows, n, Y,
-                               nullptr);
-    } else {
-        if (keep)
-            hipLaunchKernelGGL((k_mlp_fwd<true, 8>), dim3(nb(n, 128)), dim3(256), 0, s, h->wt, h->w, X, rows, n, Y,
-                               (uint16_t*)ws);
-        else
-            hipLaunchKernelGGL((k_mlp_fwd<false, 8>), dim3(nb(n, 128)), dim3(256), 0, s, h->wt, h->w, X, rows, n, Y,
-                               nullptr);
-    }
+    launch_fwd_small(h, X, rows, n, Y, keep ? (uint16_t*)ws : nullptr, s);
     RT_HIP(hipGetLastError());
     return RT_OK;
+}
+
+// The backward's two passes into the chunk partials.
+static void launch_bwd(rt_mlp* h, const uint16_t* X, const int32_t* rows, int64_t n, const float* dY, const BwdParts& b,
+                       char* base, const StepScalars& step, hipStream_t s) {
+    uint16_t* T = (uint16_t*)(base + b.t);
+    uint16_t* XT = (uint16_t*)(base + b.xt);
+    float* sp = (float*)(base + b.sp);
+    float* bp = (float*)(base + b.bp);
+    hipLaunchKernelGGL(k_bwd_signal, dim3((unsigned)b.groups), dim3(SIG_THREADS), 0, s, h->wb, h->w, X, rows, n, b.npad,
+                       (const uint16_t*)base, dY, T, XT, sp, num_xcds());
+    hipLaunchKernelGGL(k_bwd_wgrad, dim3((unsigned)(WG_JOBS * b.chunks + (step.st ? 1 : 0))), dim3(256), 0, s, T, XT, b.npad,
+                       (int)b.chunks, sp, (int)b.groups, bp, step);
 }
 
 extern "C" rt_status rt_mlp_backward(rt_mlp* h, const uint16_t* X, const int32_t* rows, int64_t n, const float* dY,
@@ -1248,17 +1442,10 @@ extern "C" rt_status rt_mlp_backward(rt_mlp* h, const uint16_t* X, const int32_t
     if (n == 0) return RT_OK;
     if (!ws || ws_bytes < ws_bytes_for(n)) return fail(RT_ERR_CAPACITY, "rt_mlp_backward: workspace too small");
     const BwdParts b = bwd_parts(n);
-    char* base = (char*)ws;
-    uint16_t* T = (uint16_t*)(base + b.t);
-    uint16_t* XT = (uint16_t*)(base + b.xt);
-    float* sp = (float*)(base + b.sp);
-    float* bp = (float*)(base + b.bp);
     hipStream_t s = (hipStream_t)stream;
-    hipLaunchKernelGGL(k_bwd_signal, dim3((unsigned)b.groups), dim3(SIG_THREADS), 0, s, h->wb, h->w, X, rows, n, b.npad,
-                       (const uint16_t*)ws, dY, T, XT, sp);
-    hipLaunchKernelGGL(k_bwd_wgrad, dim3((unsigned)(WG_JOBS * b.chunks)), dim3(256), 0, s, T, XT, b.npad,
-                       (int)b.chunks, sp, (int)b.groups, bp);
-    hipLaunchKernelGGL(k_grad_sum, dim3(nb(NPARAM, 256)), dim3(256), 0, s, bp, (int)b.chunks, h->g);
+    launch_bwd(h, X, rows, n, dY, b, (char*)ws, StepScalars{}, s);
+    hipLaunchKernelGGL(k_grad_sum, dim3(nb(NPARAM, 256)), dim3(256), 0, s, (const float*)((char*)ws + b.bp),
+                       (int)b.chunks, h->g);
     RT_HIP(hipGetLastError());
     return RT_OK;
 }
@@ -1313,21 +1500,31 @@ rt_status train_enqueue(rt_mlp* h, const uint16_t* X, const float* T, int64_t N,
     float* Y = (float*)(ws + tp.Y);
     float* dY = (float*)(ws + tp.dY);
     int64_t* st = (int64_t*)(ws + tp.st);
-    void* mws = ws + tp.mlp;
-    const size_t mbytes = ws_bytes_for(o.batch);
-    hipLaunchKernelGGL(k_train_rows, dim3(nb(o.batch, 256)), dim3(256), 0, s, st, o.seed, N, o.batch, rows);
+    char* mws = ws + tp.mlp;
+    StepScalars step = {st, nullptr, (int64_t)nb(o.batch, fwd_small(o.batch) ? 32 : 64) * (fwd_small(o.batch) ? 2 : 4),
+                        loss_sum, o};
+    if (o.batch >= WS_MIN_SAMPLES) {  // the forward for many samples stands alone
+        hipLaunchKernelGGL(k_train_rows, dim3(nb(o.batch, 256)), dim3(256), 0, s, st, o.seed, N, o.batch, rows);
+        RT_HIP(hipGetLastError());
+        rt_status e = rt_mlp_forward(h, X, rows, o.batch, Y, 1, mws, ws_bytes_for(o.batch), s);
+        if (!e) e = rt_mlp_nll(Y, T, rows, o.batch, dY, loss_sum, s);
+        if (e) return e;
+    } else {
+        const FwdTrain tr = {st, o.seed, N, T, rows, dY, Y};
+        step.loss = Y;  // the fused forward leaves Y out: its place holds the loss's partial sums
+        if (fwd_small(o.batch))
+            hipLaunchKernelGGL((k_mlp_fwd<true, 2, true>), dim3(nb(o.batch, 32)), dim3(512), 0, s, h->wt, h->w, X, nullptr,
+                               o.batch, nullptr, (uint16_t*)mws, tr);
+        else
+            hipLaunchKernelGGL((k_mlp_fwd<true, 4, true>), dim3(nb(o.batch, 64)), dim3(512), 0, s, h->wt, h->w, X, nullptr,
+                               o.batch, nullptr, (uint16_t*)mws, tr);
+        RT_HIP(hipGetLastError());
+    }
+    const BwdParts b = bwd_parts(o.batch);
+    launch_bwd(h, X, rows, o.batch, dY, b, mws, step, s);
     RT_HIP(hipGetLastError());
-    rt_status e = rt_mlp_forward(h, X, rows, o.batch, Y, 1, mws, mbytes, s);
-    if (!e) e = rt_mlp_nll(Y, T, rows, o.batch, dY, loss_sum, s);
-    if (e) return e;
-    hipLaunchKernelGGL(k_zero_f32, dim3(nb(NPARAM, 256)), dim3(256), 0, s, h->g, NPARAM);
-    e = rt_mlp_backward(h, X, rows, o.batch, dY, mws, mbytes, s);
-    if (e) return e;
-    hipLaunchKernelGGL(k_adam_sched, dim3(nb(NPARAM, 256)), dim3(256), 0, s, h->w, h->g, h->m, h->v, st, o);
-    RT_HIP(hipGetLastError());
-    e = mlp_publish(h, s);
-    if (e) return e;
-    hipLaunchKernelGGL(k_step_inc, dim3(1), dim3(64), 0, s, st);
+    hipLaunchKernelGGL(k_train_step, dim3(STEP_TILES + nb(STEP_REST, 256)), dim3(256), 0, s, (const float*)(mws + b.bp),
+                       (int)b.chunks, h->w, h->g, h->m, h->v, h->wt, h->wb, st, o);
     RT_HIP(hipGetLastError());
     return RT_OK;
 }
