@@ -409,6 +409,12 @@ __device__ inline void substep_interval(const ItemCtx& c, SweepState<T>& st, boo
     row_s<T, SCH>(st, fr, (cp + cn) * hh, cp, ep, cn, en, I);
 }
 
+// REF of the refined kernels: which refinements the launch asks for.  Kernels for one alone do without
+// the other's state (the FP64 split decision's table values, the interval's FP64 ends) and so hold more
+// waves: with the sub-points below, the 10k-point wind's sweep in FP32 with velocity sampling 3.55 -> 2.52
+// ms, in FP64 with fourth-order rows and optical depths 5.35 -> 4.74 ms.
+constexpr int REF_TAU = 1, REF_DV = 2;
+
 // The stream of line points of one side, far to near, after velocity sampling.
 template <typename T>
 struct Emitter {
@@ -420,18 +426,18 @@ struct Emitter {
 
 // Emit the next line point; the interval from the previous one (hds: its length times
 // half_step, FP64 length ds64) is split by optical depth when that is on.
-template <typename T, int SCH>
+template <typename T, int SCH, int REF>
 __device__ inline void emit_point(const ItemCtx& c, SweepState<T>& st, Emitter<T>& em, T cn, T en,
                                   const Pt64<T>& pn, T hds, double ds64, T I) {
     if (em.have) {
-        if (c.dtau_rcp > 0.0)
+        if (REF & REF_TAU)
             substep_interval<T, SCH>(c, st, em.first, em.c, em.e, cn, en, hds, em.p, pn, ds64, I);
         else row_s<T, SCH>(st, em.first, (em.c + cn) * hds, em.c, em.e, cn, en, I);
         em.first = false;
     }
     em.c = cn;
     em.e = en;
-    em.p = pn;
+    if (REF & REF_TAU) em.p = pn;
     em.have = true;
 }
 
@@ -448,18 +454,18 @@ struct RealPt {
 // times half_step and FP64 length: velocity sub-points first (m from |p_C - p_P|), each emitted,
 // then C itself.  fwd: this side is the +n ray, whose nearer point has the
 // smaller line coordinate (so it is the interval's point a).
-template <typename T, bool UDX, int SCH>
+template <typename T, bool UDX, int SCH, int REF>
 __device__ inline void real_interval(const ItemCtx& c, SweepState<T>& st, Emitter<T>& em, const RealPt<T>& P,
                                      const RealPt<T>& C, T hds, double ds64, bool fwd, const LaneFreq& lf, T I) {
     int m = 1;
-    if (c.dv_rcp > 0.0) {
+    if (REF & REF_DV) {
         double q = ceil(fabs(C.dot - P.dot) * c.dv_rcp);
         if (q > (double)c.max_sub) q = (double)c.max_sub;
         m = q >= 1.0 ? (int)q : 1;
         m = __builtin_amdgcn_readfirstlane(m);  // the same in every lane
     }
-    if (m == 1) {
-        emit_point<T, SCH>(c, st, em, C.c, C.e, C.p, hds, ds64, I);
+    if (!(REF & REF_DV) || m == 1) {
+        emit_point<T, SCH, REF>(c, st, em, C.c, C.e, C.p, hds, ds64, I);
         return;
     }
     const T hs = hds * rcp<T>((T)m);
@@ -470,14 +476,32 @@ __device__ inline void real_interval(const ItemCtx& c, SweepState<T>& st, Emitte
     const int lb_bytes = (lf.fb + lf.fl) * (int)sizeof(T);
     const int lo_bytes = lf.fb * (int)sizeof(T);
     const int hi_bytes = (lf.fb + lf.L - 1) * (int)sizeof(T);
-    for (int jj = 1; jj < m; ++jj) {  // far to near
+    const auto sub_point = [&](int jj, double& w, int& k, double& t64) {  // weight, whole shift, its fraction
         const int jo = fwd ? m - jj : jj;
-        const double w = (double)jo / (double)m;
+        w = (double)jo / (double)m;
         const double vdot = (1.0 - w) * A.dot + w * B.dot;
         const double delta = vdot / dx;
         const double kf = floor(delta);
-        const int k = (int)kf;
-        const double t64 = delta - kf;
+        k = (int)kf;
+        t64 = delta - kf;
+    };
+    double w_l = 0.0, t_l = 0.0;
+    int k_l = 0;
+    const int lane = threadIdx.x & 63;
+    for (int jj = 1; jj < m; ++jj) {  // far to near
+        double w, t64;
+        int k;
+        // the same in every lane: 64 sub-points formed at once, one per lane (3.53 -> 3.05 ms of that wind's sweep
+        // in FP32 against two FP64 divisions per sub-point in every lane)
+        if (UDX) {
+            const int at = (jj - 1) & 63;
+            if (at == 0) sub_point(jj + lane, w_l, k_l, t_l);
+            w = readlane_d(w_l, at);
+            t64 = readlane_d(t_l, at);
+            k = __builtin_amdgcn_readlane(k_l, at);
+        } else {
+            sub_point(jj, w, k, t64);
+        }
         const T t = (T)t64;
         const int ks = k * (int)sizeof(T);
         const uint32_t oa = (uint32_t)clamp_i32(lb_bytes - ks, lo_bytes, hi_bytes);
@@ -491,9 +515,9 @@ __device__ inline void real_interval(const ItemCtx& c, SweepState<T>& st, Emitte
         const T ya = fma_<T>(t, g1 - g0, g0), yb = fma_<T>(t, h1 - h0, h0);
         const T cv = fma_<T>(wt, xb - xa, xa);
         const T ev = fma_<T>(wt, yb - ya, ya);
-        emit_point<T, SCH>(c, st, em, cv, ev, Pt64<T>{a0, a1, b0, b1, t64, w}, hs, ds64s, I);
+        emit_point<T, SCH, REF>(c, st, em, cv, ev, Pt64<T>{a0, a1, b0, b1, t64, w}, hs, ds64s, I);
     }
-    emit_point<T, SCH>(c, st, em, C.c, C.e, C.p, hs, ds64s, I);
+    emit_point<T, SCH, REF>(c, st, em, C.c, C.e, C.p, hs, ds64s, I);
 }
 
 // One side of the line with velocity sampling and/or optical-depth sub-steps
@@ -503,7 +527,7 @@ __device__ inline void real_interval(const ItemCtx& c, SweepState<T>& st, Emitte
 // list point, 6 the whole-step shift (uniform dx), 8-9 its FP64 fraction.
 constexpr int REF_STAGE_WORDS = 12;
 
-template <typename T, bool MOVING, bool UDX, int SCH>
+template <typename T, bool MOVING, bool UDX, int SCH, int REF>
 __device__ inline void sweep_ref(const ItemCtx& c, int64_t base, int n, const LaneFreq& lf, int lane, bool fwd,
                                  T chi_o, T eta_o, T I, SweepState<T>& st, uint32_t* stage) {
     Emitter<T> em;
@@ -602,8 +626,8 @@ __device__ inline void sweep_ref(const ItemCtx& c, int64_t base, int n, const La
                 cur.e = f.ea;
                 cur.p = Pt64<T>{cur.c, cur.c, cur.c, cur.c, 0.0, 0.0};
             }
-            if (done == 0) emit_point<T, SCH>(c, st, em, cur.c, cur.e, cur.p, (T)0, 0.0, I);
-            else real_interval<T, UDX, SCH>(c, st, em, prev, cur, hds_prev, ds64_prev, fwd, lf, I);
+            if (done == 0) emit_point<T, SCH, REF>(c, st, em, cur.c, cur.e, cur.p, (T)0, 0.0, I);
+            else real_interval<T, UDX, SCH, REF>(c, st, em, prev, cur, hds_prev, ds64_prev, fwd, lf, I);
             prev = cur;
             ds64_prev = ds64;
             hds_prev = (T)(half_step<SCH>() * ds64);
@@ -618,7 +642,7 @@ __device__ inline void sweep_ref(const ItemCtx& c, int64_t base, int n, const La
         org.p = Pt64<T>{chi_o, chi_o, chi_o, chi_o, 0.0, 0.0};
         org.dot = 0.0;
         org.row = c.row_o;
-        real_interval<T, UDX, SCH>(c, st, em, prev, org, hds_prev, ds64_prev, fwd, lf, I);
+        real_interval<T, UDX, SCH, REF>(c, st, em, prev, org, hds_prev, ds64_prev, fwd, lf, I);
     }
 }
 
@@ -935,7 +959,7 @@ __device__ inline void solve_item_half(const SolveLaunch& a, int64_t oi, int64_t
     }
 }
 
-template <typename T, bool MOVING, bool UDX, int GROUP, bool REF, int SCH, bool PACK>
+template <typename T, bool MOVING, bool UDX, int GROUP, int REF, int SCH, bool PACK>
 __device__ inline void solve_item(const SolveLaunch& a, int64_t w, int nfc, int lane, uint32_t* stage) {
     // w is the same in every lane of the wave
     w = uni64(w);
@@ -986,8 +1010,8 @@ __device__ inline void solve_item(const SolveLaunch& a, int64_t w, int nfc, int 
     const T S_o = eta_o * rcp<T>(chi_o);
     SweepState<T> m{}, p{};
     if (REF) {
-        sweep_ref<T, MOVING, UDX, SCH>(c, bm, nm, lf, lane, false, chi_o, eta_o, I, m, stage);
-        sweep_ref<T, MOVING, UDX, SCH>(c, bp, np, lf, lane, true, chi_o, eta_o, I, p, stage);
+        sweep_ref<T, MOVING, UDX, SCH, REF>(c, bm, nm, lf, lane, false, chi_o, eta_o, I, m, stage);
+        sweep_ref<T, MOVING, UDX, SCH, REF>(c, bp, np, lf, lane, true, chi_o, eta_o, I, p, stage);
     } else {
         if (a.small_tables) {
             sweep<T, MOVING, UDX, GROUP, true, SCH>(c, bm, nm, lf, lane, chi_o, eta_o, I, m, stage);
@@ -1020,20 +1044,25 @@ __device__ inline void solve_item(const SolveLaunch& a, int64_t w, int nfc, int 
 // half-wave variant fits 80 (6 waves, two spilled; the 507k-leaf octree 747 ms against
 // 762 with groups of 8 at 4 waves).  The refined sweeps take the bounds below; the
 // others keep the compiler's choice (held to 64 registers they spill heavily).
-template <typename T, bool UDX, int GROUP, bool REF, int SCH, bool PACK>
+template <typename T, bool UDX, int GROUP, int REF, int SCH, bool PACK>
 constexpr int solve_direct_waves() {
     if (!UDX || GROUP != 4) return 1;
-    // refined lines (measured on the 50k wind at dtau_max = 1, spills 0): FP32 second-order rows at 5 waves
-    // (39.7 -> 38.6 ms; 6 waves 47.1), fourth-order at 4 (70.8 -> 59.6 ms), FP64 at 3 (78.9 -> 59.1 and
-    // 113.5 -> 94.2 ms); the plain FP64 sweep keeps the compiler's choice (43.3 ms against 44.4 at 5 waves)
-    if (REF) return sizeof(T) == 4 ? (SCH == 0 ? 5 : 4) : 3;
+    // refined lines with both refinements (measured on the 50k wind at dtau_max = 1): FP32 second-order rows
+    // at 5 waves (39.7 -> 38.6 ms; 6 waves 47.1), fourth-order at 4 (70.8 -> 59.6 ms), FP64 at 3 (78.9 -> 59.1
+    // and 113.5 -> 94.2 ms); the plain FP64 sweep keeps the compiler's choice (43.3 ms against 44.4 at 5 waves)
+    if (REF == (REF_TAU | REF_DV)) return sizeof(T) == 4 ? (SCH == 0 ? 5 : 4) : 3;
+    // one refinement alone holds less (10k-point wind, 24 pairs, 64 frequencies, velocity sampling at 1/3
+    // Doppler width and optical depth at 1, ms): FP32 second-order at 6 waves 2.52 and 1.38 (5: 2.57, 1.42),
+    // fourth-order at 5 waves 4.39 and 3.11 (4: 4.59, 3.29), FP64 at 4 waves 5.78 and 2.24, fourth-order 6.79
+    // and 4.74 (3: 5.88, 2.40, 7.21, 5.07)
+    if (REF) return sizeof(T) == 4 ? (SCH == 0 ? 6 : 5) : 4;
     return (sizeof(T) == 4 && SCH == 0) ? (PACK ? 6 : 8) : 1;
 }
 
-template <typename T, bool MOVING, bool UDX, int GROUP, bool REF, int SCH, bool PACK>
+template <typename T, bool MOVING, bool UDX, int GROUP, int REF, int SCH, bool PACK>
 __global__ __launch_bounds__(SOLVE_BLOCK, (solve_direct_waves<T, UDX, GROUP, REF, SCH, PACK>())) void k_solve_direct(
     const SolveLaunch a) {
-    constexpr int WORDS = REF ? REF_STAGE_WORDS : STAGE_WORDS;
+    constexpr int WORDS = REF != 0 ? REF_STAGE_WORDS : STAGE_WORDS;
     __shared__ uint32_t stage_all[WAVES_PER_BLOCK * 64 * WORDS];
     uint32_t* stage = stage_all + (threadIdx.x >> 6) * 64 * WORDS;
     const int lane = threadIdx.x & 63;
@@ -1060,9 +1089,9 @@ __global__ __launch_bounds__(SOLVE_BLOCK, (solve_direct_waves<T, UDX, GROUP, REF
 // takes the next PERSIST_CHUNK items with one atomic (one counter shared by
 // every wave: an atomic per item serialised the queue) and exits when the
 // queue is empty, so every wave reaches the end.
-template <typename T, bool MOVING, bool UDX, int GROUP, bool REF, int SCH, bool PACK>
+template <typename T, bool MOVING, bool UDX, int GROUP, int REF, int SCH, bool PACK>
 __global__ __launch_bounds__(SOLVE_BLOCK) void k_solve_persist(const SolveLaunch a) {
-    constexpr int WORDS = REF ? REF_STAGE_WORDS : STAGE_WORDS;
+    constexpr int WORDS = REF != 0 ? REF_STAGE_WORDS : STAGE_WORDS;
     __shared__ uint32_t stage_all[WAVES_PER_BLOCK * 64 * WORDS];
     uint32_t* stage = stage_all + (threadIdx.x >> 6) * 64 * WORDS;
     const int lane = threadIdx.x & 63;
@@ -1685,7 +1714,7 @@ hipError_t launch_bin(const SolveLaunch& a0, void* ws, int32_t** items_out, hipS
     return hipGetLastError();
 }
 
-template <typename T, int G, bool REF, int SCH, bool PACK>
+template <typename T, int G, int REF, int SCH, bool PACK>
 static void solve_dispatch_g(const SolveLaunch& a, bool persist, dim3 grid, hipStream_t s) {
     const bool moving = a.vel != nullptr;
     // the shift of a point is lane-independent when every block has the same dx
@@ -1707,21 +1736,28 @@ static void solve_dispatch_g(const SolveLaunch& a, bool persist, dim3 grid, hipS
 template <typename T>
 static void solve_dispatch(const SolveLaunch& a, bool persist, dim3 grid, hipStream_t s) {
     // refined lines (velocity sampling, optical-depth sub-steps) take their own sweep
-    const bool ref = a.dtau_max_rcp > 0.0 || a.dv_max_rcp > 0.0;
+    const int ref = (a.dtau_max_rcp > 0.0 ? REF_TAU : 0) | (a.dv_max_rcp > 0.0 ? REF_DV : 0);
     // 65..96 frequencies: the second chunks of two pairs share a wave (solve_item_half)
     const bool pack = a.F > 64 && a.F <= 96 && (a.R & 1) == 0 && a.small_tables;
+#define RT_REFINED(SCH)                                                                 \
+    do {                                                                                \
+        if (ref == REF_TAU) solve_dispatch_g<T, 4, REF_TAU, SCH, false>(a, persist, grid, s); \
+        else if (ref == REF_DV) solve_dispatch_g<T, 4, REF_DV, SCH, false>(a, persist, grid, s); \
+        else solve_dispatch_g<T, 4, REF_TAU | REF_DV, SCH, false>(a, persist, grid, s); \
+    } while (0)
     if (a.scheme == RT_SCHEME_HERMITE) {  // fourth-order rows: one load group size
-        if (ref) solve_dispatch_g<T, 4, true, 1, false>(a, persist, grid, s);
-        else solve_dispatch_g<T, 4, false, 1, false>(a, persist, grid, s);
+        if (ref) RT_REFINED(1);
+        else solve_dispatch_g<T, 4, 0, 1, false>(a, persist, grid, s);
     } else if (ref) {
-        solve_dispatch_g<T, 4, true, 0, false>(a, persist, grid, s);
+        RT_REFINED(0);
     } else if (a.group == 4) {
-        if (pack) solve_dispatch_g<T, 4, false, 0, true>(a, persist, grid, s);
-        else solve_dispatch_g<T, 4, false, 0, false>(a, persist, grid, s);
+        if (pack) solve_dispatch_g<T, 4, 0, 0, true>(a, persist, grid, s);
+        else solve_dispatch_g<T, 4, 0, 0, false>(a, persist, grid, s);
     } else {
-        if (pack) solve_dispatch_g<T, 8, false, 0, true>(a, persist, grid, s);
-        else solve_dispatch_g<T, 8, false, 0, false>(a, persist, grid, s);
+        if (pack) solve_dispatch_g<T, 8, 0, 0, true>(a, persist, grid, s);
+        else solve_dispatch_g<T, 8, 0, 0, false>(a, persist, grid, s);
     }
+#undef RT_REFINED
 }
 
 // Values per lane of the multi-line sweep for this launch's frequencies, lanes per line, lines per wave and
