@@ -36,7 +36,7 @@
 // sqrt 2, which leaves every formula above as it is but for (a+b)/2, now a + b,
 // and G = r = 1, Y = I before the far end, now G = sqrt 2, Y = sqrt 2 I.  With S_d
 // = e/c the row's two quotients share the reciprocal q = 1/(D c), D = 1 + b G:
-//     r = q c,  Y = (h e + c Y_{d-1}) q,  h = a + b:
+//     r = q c,  Y = (h q) e + r Y_{d-1},  h = a + b:
 // ten operations and one reciprocal.  A line starts from that state with c = 1,
 // e = 0 and no step, for which the row changes nothing, exactly; so every point
 // takes the same row, the first included.
@@ -180,7 +180,9 @@ __device__ inline void row2_start(Row2<T>& st, T I) {
 }
 
 // The row of the point with opacity c and emissivity e, given its inner step b.  (D >= 1 and c > 0, so
-// D c neither cancels nor, for opacities below ~1e30, overflows.)
+// D c neither cancels nor, for FP32 opacities below ~1e30, overflows at moderate steps; where it does
+// because D ~ b^2 is large, r and Y are zero to within rounding of the next row's h.  h q e and r Y are as
+// large as what they add to Y, so thin points with small emissivities do not underflow on the way.)
 template <typename T>
 __device__ inline void row2(Row2<T>& st, T b, T c, T e) {
     const T h = st.a + b;
@@ -188,7 +190,7 @@ __device__ inline void row2(Row2<T>& st, T b, T c, T e) {
     const T D = fma_<T>(b, st.G, (T)1);
     const T q = rcp<T>(D * c);
     st.r = q * c;
-    st.Y = fma_<T>(h, e, c * st.Y) * q;
+    st.Y = fma_<T>(h * q, e, st.r * st.Y);
     st.a = b;
 }
 
