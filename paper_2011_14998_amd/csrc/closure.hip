@@ -857,7 +857,7 @@ __device__ inline void step_scalars(const StepScalars& q, float* red) {
             if (t < h) red[t] += red[t + h];
             __syncthreads();
         }
-        if (t == 0) *q.loss_sum += red[0];
+        if (t == 0) atomicAdd(q.loss_sum, red[0]);  // another training on another stream may add to it
     }
     if (t != 0) return;
     const rt_train_opts& o = q.o;
