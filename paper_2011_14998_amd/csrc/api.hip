@@ -1229,6 +1229,14 @@ rt_status rt::plan_create_ordered(const rt_model* m, rt_dirset* set, const int32
         plan_free(p);
         return st;
     }
+    const size_t es = p->o.precision == RT_F64 ? 8 : 4;
+    p->u_bytes = es * (size_t)std::max<int64_t>(n_origins * set->R * p->a.F, 1);
+    e = pool_alloc(&p->u_buf, p->u_bytes);
+    if (e != hipSuccess) {
+        st = hip_fail(e, "rt_plan_create: u buffer");
+        plan_free(p);
+        return st;
+    }
     // Moving media: the multi-line sweep reads padded copies of the tables, remade by every run.  A row's
     // copy costs about what the sweep of 16 of its line points saves, so models that the lists visit
     // less than 32 times per point keep the caller's tables (and so they do without memory for copies).
@@ -1243,16 +1251,14 @@ rt_status rt::plan_create_ordered(const rt_model* m, rt_dirset* set, const int32
         }
     }
     p->base = p->a;
-    const size_t es = p->o.precision == RT_F64 ? 8 : 4;
-    p->u_bytes = es * (size_t)std::max<int64_t>(n_origins * set->R * p->a.F, 1);
-    e = pool_alloc(&p->u_buf, p->u_bytes);
-    if (e != hipSuccess) {
-        st = hip_fail(e, "rt_plan_create: u buffer");
-        plan_free(p);
-        return st;
-    }
     p->stream = s;
     st = plan_configure(p, p->o);
+    if (st && p->pad) {  // perhaps the copies took the memory it needed
+        (void)hipGetLastError();
+        (void)hipFree(p->pad);
+        p->pad = p->base.pad_chi = p->base.pad_eta = nullptr;
+        st = plan_configure(p, p->o);
+    }
     if (st) {
         plan_free(p);
         return st;
