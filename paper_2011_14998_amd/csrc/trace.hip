@@ -253,17 +253,38 @@ __device__ inline void exact_stage(double& D, int& i, uint32_t& code) {
     code = take ? co : code;
 }
 
+// What the FP32 filter knows of a step: the current point's offset from the axis, the direction, the
+// bound on an edge's projection.
+struct Filter {
+    float px, py, pz, fx, fy, fz, tol_s;
+    // a candidate's projection from the current point and squared distance from the axis
+    __device__ void eval(const RowRec& q, float& s, float& D) const {
+        const float tx = px + q.ex, ty = py + q.ey, tz = pz + q.ez;
+        s = __builtin_fmaf(q.ez, fz, __builtin_fmaf(q.ey, fy, q.ex * fx));
+        D = __builtin_fmaf(-s, s, __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx)));
+    }
+};
+
+// Only the candidates that the filter leaves: on an octree's lattice, where ties and edges across the ray
+// are common, reading the heads of those alone takes the walk of 50k leaves (96 pairs, 22 neighbours)
+// from 20.1 to 17.3 ms.  (Leaving out edges across the ray that end far from the axis before coming here
+// costs 6 registers and with them a wave per SIMD: wind 5.6 -> 6.1 ms, the octree no faster.)
 template <int GL>
-__device__ inline bool exact_step(const RowTab t, const char* row, int pieces, int sub, double ox, double oy, double oz,
-                                  double dx, double dy, double dz, double Zc, uint32_t& code) {
+__device__ inline bool exact_step(const RowTab t, const char* row, int pieces, int sub, const Filter& flt, float lim_D,
+                                  double ox, double oy, double oz, double dx, double dy, double dz, double Zc,
+                                  uint32_t& code) {
     double D = __builtin_inf();
     int best = INT32_MAX;
     uint32_t c = 0;
     for (int i = sub; i < pieces; i += GL) {
         if (i < 2) continue;  // the head
         const RowRec* rec = (const RowRec*)row + i;
-        if (rec->ex != rec->ex) continue;  // blank
-        const uint32_t ck = rec->code;
+        const RowRec q = *rec;
+        if (q.ex != q.ex) continue;  // blank
+        float fs, fD;
+        flt.eval(q, fs, fD);
+        if (fs < -flt.tol_s || fD > lim_D) continue;
+        const uint32_t ck = q.code;
         const RowHead* h = (const RowHead*)(t.recs + t.offset(ck));
         const double Rx = h->x - ox, Ry = h->y - oy, Rz = h->z - oz;
         const double Zk = __builtin_fma(Rz, dz, __builtin_fma(Ry, dy, Rx * dx));
@@ -474,6 +495,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(
         D2 = unsure ? -inf : D2;
         const float least = group_reduce<GL>(D1, [](float a, float o) { return o < a ? o : a; });
         const float lim_D = least + tol_D;
+        const Filter flt = {px, py, pz, fx, fy, fz, tol_s};
         // candidates that may be the rule's choice: one means it is known
         const bool mine = D1 <= lim_D;
         const int rivals = group_reduce<GL>((mine ? 1 : 0) + (D2 <= lim_D ? 2 : 0), [](int a, int o) { return a + o; });
@@ -481,7 +503,7 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(
         if (rivals != 1) {
             // none forward (D1 = D2 = inf in every lane): the ray leaves the model
             if (least == inf && group_reduce<GL>(D2, [](float a, float o) { return o < a ? o : a; }) == inf) break;
-            if (!exact_step<GL>(t, row, pieces, sub, ox, oy, oz, dx, dy, dz, Z, code)) break;
+            if (!exact_step<GL>(t, row, pieces, sub, flt, lim_D, ox, oy, oz, dx, dy, dz, Z, code)) break;
         }
     }
     if (MODE != TRACE_COUNT) {
