@@ -51,7 +51,7 @@ TUNED = {
 
 
 SCHEDULE_NAMES = {0: "direct launch in slot order", 1: "length-binned persistent launch",
-                  2: "direct launch direction by direction over Morton-ordered origins, XCD runs of 16 (walk) and 256 (sweep) workgroups"}
+                  2: "direct launch direction by direction over Morton-ordered origins, XCD runs of 16 (walk) and 64 (sweep) workgroups"}
 
 
 def _log(msg):
@@ -68,10 +68,10 @@ def sweep_bytes(n_origins, R, total_entries, F, moving, es=4):
 
 
 def walk_bytes(n_rays, total_entries, mean_degree):
-    """Algorithmic bytes of one walk launch: every step reads the current point's row of
-    32-byte neighbour records (mean degree of the model), and each list entry reads one id
-    and writes 12 bytes; a ray takes one step per entry plus the step that ends it."""
-    return (total_entries + n_rays) * mean_degree * 32 + total_entries * 16
+    """Algorithmic bytes of one walk launch: every step reads the current point's row (a 32-byte
+    head and 16-byte neighbour records, mean degree of the model), and each list entry writes 12
+    bytes; a ray takes one step per entry plus the step that ends it."""
+    return (total_entries + n_rays) * (32 + mean_degree * 16) + total_entries * 12
 
 
 def src_hash(*names):
@@ -84,7 +84,7 @@ def src_hash(*names):
 
 SWEEP_SRC = ("solve.hip", "rt_internal.h")
 WALK_SRC = ("trace.hip", "rt_internal.h")
-KERNEL_KEYS = {"sweep": ("k_solve_direct", "k_solve_persist"), "walk": ("k_trace<1", "k_trace<2"),
+KERNEL_KEYS = {"sweep": ("k_solve_lines", "k_solve_direct", "k_solve_persist"), "walk": ("k_trace<1", "k_trace<2"),
                "compact": ("k_compact",), "reduce": ("k_reduce",), "gather": ("k_batch_gather",)}
 
 
@@ -340,8 +340,8 @@ def _roofline_walk(workload, stages, alg):
     elif path:
         r["measured"] += " (taken on another walk source: not used)"
     r["algorithmic"] = {"bytes_per_launch": alg, "gbs": alg / walk_s / 1e9, "frac": alg / walk_s / 1e9 / HBM_PEAK_GBS,
-                        "model": "per step the current point's row of 32-byte neighbour records at the model's mean "
-                                 "degree, per list entry a 4-byte id read and 12 bytes written; re-reads served by "
+                        "model": "per step the current point's row (a 32-byte head, 16-byte neighbour records at "
+                                 "the model's mean degree), per list entry 12 bytes written; re-reads served by "
                                  "the caches count too"}
     return r
 
