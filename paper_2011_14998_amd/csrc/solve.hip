@@ -36,7 +36,7 @@
 // sqrt 2, which leaves every formula above as it is but for (a+b)/2, now a + b,
 // and G = r = 1, Y = I before the far end, now G = sqrt 2, Y = sqrt 2 I.  With S_d
 // = e/c the row's two quotients share the reciprocal q = 1/(D c), D = 1 + b G:
-//     r = q c,  Y = (h q) e + r Y_{d-1},  h = a + b:
+//     r = q c,  Y = h (q e) + r Y_{d-1},  h = a + b:
 // ten operations and one reciprocal.  A line starts from that state with c = 1,
 // e = 0 and no step, for which the row changes nothing, exactly; so every point
 // takes the same row, the first included.
@@ -179,10 +179,11 @@ __device__ inline void row2_start(Row2<T>& st, T I) {
     st.Y = (T)SQRT2 * I;
 }
 
-// The row of the point with opacity c and emissivity e, given its inner step b.  (D >= 1 and c > 0, so
-// D c neither cancels nor, for FP32 opacities below ~1e30, overflows at moderate steps; where it does
-// because D ~ b^2 is large, r and Y are zero to within rounding of the next row's h.  h q e and r Y are as
-// large as what they add to Y, so thin points with small emissivities do not underflow on the way.)
+// The row of the point with opacity c and emissivity e, given its inner step b.  D >= 1 and c > 0, so D c does
+// not cancel.  The order of the products keeps FP32 in range wherever u is: q e = S/D is at most the point's
+// source, h q e and r Y are what is added to Y (h q alone is a length, past FP32's range where an outer step of
+// 1e4 meets an opacity of 1e-35; h e and c Y lose thin points of small emissivity).  Where q e or, beyond D c ~
+// 1e38, q itself underflows, D ~ b^2 is large and what is lost lies below the rounding of the next row's h S.
 template <typename T>
 __device__ inline void row2(Row2<T>& st, T b, T c, T e) {
     const T h = st.a + b;
@@ -190,7 +191,7 @@ __device__ inline void row2(Row2<T>& st, T b, T c, T e) {
     const T D = fma_<T>(b, st.G, (T)1);
     const T q = rcp<T>(D * c);
     st.r = q * c;
-    st.Y = fma_<T>(h * q, e, st.r * st.Y);
+    st.Y = fma_<T>(h, q * e, st.r * st.Y);
     st.a = b;
 }
 
