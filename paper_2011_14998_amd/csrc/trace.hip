@@ -165,11 +165,12 @@ __global__ __launch_bounds__(256) void k_check_off(const int64_t* __restrict__ o
 // scaled by a power of two so that every coordinate is below 1 where FP32's
 // range calls for it.  So a candidate with s < -tol_s is not forward, one with
 // s > tol_s is, and D orders two candidates when their FP32 values are more
-// than tol_D apart.  When no candidate lies between the two and the best
-// forward one is ahead of the second by more than tol_D, it is the FP64 rule's
-// choice; otherwise (about one step in 10^4 on irregular points; ties on
-// lattices) the group evaluates the rule itself in FP64 over the row
-// (exact_step).  The lists are those of the FP64 rule, bit for bit.
+// than tol_D apart.  When the candidate of least D among those with s >= -tol_s
+// has s > tol_s and is ahead of the second by more than tol_D, it is the FP64
+// rule's choice; otherwise (about one step in 10^4 on irregular points, one in
+// 20 on an octree: edges across the ray that end near the axis, and ties) the
+// group evaluates the rule itself in FP64 over those that are left (exact_step).
+// The lists are those of the FP64 rule, bit for bit.
 //
 // What bounds it: VALU issue, ~170 instructions per step of a wave's 16 rays
 // (17 FP32 ones per candidate; the rule in FP64 takes ~20, most of them at
@@ -178,9 +179,12 @@ __global__ __launch_bounds__(256) void k_check_off(const int64_t* __restrict__ o
 // row's end read blank records, and whether a wave takes a fifth or sixth
 // piece is a scalar branch; loads under exec masks made the compiler wait for
 // some before it issued the rest (7.9 ms).  50 000-point cloud, 96 pairs,
-// 2.6e8 steps: 5.5 ms (46e9 steps/s), against 9.4 ms with every candidate's
-// FP64 record (32 bytes) read and weighed; 26-neighbour grid, 5.0e8 steps: 9.8
-// ms against 16.3.
+// 2.6e8 steps: 5.6 ms (46e9 steps/s), against 9.4 ms with every candidate's
+// FP64 record (32 bytes) read and weighed; 26-neighbour grid, 5.0e8 steps: 10.0
+// ms against 16.4; 50 000 leaves of an octree, 4.1e8 steps: 10.7 against 15.1,
+// and bare lists of 20 000 of them at 24 pairs, whose waves mix directions, 4.2
+// against 4.25 (17.4 and 10.1 where any edge across the ray, however far its end,
+// sent the group to a rule that read its row again).
 //
 // List entries are buffered across the group and written in blocks of RUNL =
 // max(GL, 8) entries aligned to absolute list positions (ids 32 or 64 bytes, Z
@@ -254,48 +258,68 @@ __device__ inline void exact_stage(double& D, int& i, uint32_t& code) {
 }
 
 // What the FP32 filter knows of a step: the current point's offset from the axis, the direction, the
-// bound on an edge's projection.
+// bounds on an edge's projection and a squared distance.
 struct Filter {
-    float px, py, pz, fx, fy, fz, tol_s;
+    float px, py, pz, fx, fy, fz, tol_s, tol_D;
     // a candidate's projection from the current point and squared distance from the axis
-    __device__ void eval(const RowRec& q, float& s, float& D) const {
-        const float tx = px + q.ex, ty = py + q.ey, tz = pz + q.ez;
-        s = __builtin_fmaf(q.ez, fz, __builtin_fmaf(q.ey, fy, q.ex * fx));
+    __device__ void eval(const f32x4 q, float& s, float& D) const {
+        const float tx = px + q.x, ty = py + q.y, tz = pz + q.z;
+        s = __builtin_fmaf(q.z, fz, __builtin_fmaf(q.y, fy, q.x * fx));
         D = __builtin_fmaf(-s, s, __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx)));
     }
 };
 
-// Only the candidates that the filter leaves: on an octree's lattice, where ties and edges across the ray
-// are common, reading the heads of those alone takes the walk of 50k leaves (96 pairs, 22 neighbours)
-// from 20.1 to 17.3 ms.  (Leaving out edges across the ray that end far from the axis before coming here
-// costs 6 registers and with them a wave per SIMD: wind 5.6 -> 6.1 ms, the octree no faster.)
-template <int GL>
-__device__ inline bool exact_step(const RowTab t, const char* row, int pieces, int sub, const Filter& flt, float lim_D,
-                                  double ox, double oy, double oz, double dx, double dy, double dz, double Zc,
-                                  uint32_t& code) {
+// The rule over the candidates that the filter leaves.  The whole wave waits for its undecided groups, so the
+// row's records are not read again: rec holds those of the first pass (cols per lane), and only the heads of
+// the candidates left, mostly one or two in a group, are loaded, a round for each that a lane has.
+template <int GL, int UW>
+__device__ inline bool exact_step(const RowTab t, const char* row, const f32x4 (&rec)[UW], int cols, int pieces,
+                                  int sub, const Filter flt, double ox, double oy, double oz, double dx, double dy,
+                                  double dz, double Zc, uint32_t& code) {
     double D = __builtin_inf();
     int best = INT32_MAX;
     uint32_t c = 0;
-    for (int i = sub; i < pieces; i += GL) {
-        if (i < 2) continue;  // the head
-        const RowRec* rec = (const RowRec*)row + i;
-        const RowRec q = *rec;
-        if (q.ex != q.ex) continue;  // blank
-        float fs, fD;
-        flt.eval(q, fs, fD);
-        if (fs < -flt.tol_s || fD > lim_D) continue;
-        const uint32_t ck = q.code;
+    auto weigh = [&](int i, uint32_t ck) {
         const RowHead* h = (const RowHead*)(t.recs + t.offset(ck));
         const double Rx = h->x - ox, Ry = h->y - oy, Rz = h->z - oz;
         const double Zk = __builtin_fma(Rz, dz, __builtin_fma(Ry, dy, Rx * dx));
-        if (!(Zk > Zc)) continue;
         const double qx = __builtin_fma(-Zk, dx, Rx), qy = __builtin_fma(-Zk, dy, Ry), qz = __builtin_fma(-Zk, dz, Rz);
         const double Dk = __builtin_fma(qz, qz, __builtin_fma(qy, qy, qx * qx));
-        if (Dk < D) {  // ascending places within the lane: the first of equal D stays
+        if (Zk > Zc && Dk < D) {  // ascending places within the lane: the first of equal D stays
             D = Dk;
             best = i;
             c = ck;
         }
+    };
+    float least = __builtin_inff(), fs, fD, fDk[UW];  // the least D of those surely forward
+#pragma unroll
+    for (int k = 0; k < UW; ++k)
+        if (k < cols) {
+            flt.eval(rec[k], fs, fD);
+            fDk[k] = fs >= -flt.tol_s ? fD : NAN;
+            least = fs > flt.tol_s && fD < least ? fD : least;
+        }
+    for (int i = sub + UW * GL; i < pieces; i += GL) {
+        flt.eval(*(const f32x4*)(row + (int64_t)i * 16), fs, fD);
+        least = fs > flt.tol_s && fD < least ? fD : least;
+    }
+    const float lim_D = group_reduce<GL>(least, [](float a, float o) { return o < a ? o : a; }) + flt.tol_D;
+    uint32_t left = 0;
+#pragma unroll
+    for (int k = 0; k < UW; ++k)
+        if (k < cols) left |= (fDk[k] <= lim_D ? 1u : 0u) << k;
+    while (left) {
+        const int k = __builtin_ctz(left);
+        left &= left - 1;
+        float ck = rec[0].w;
+#pragma unroll
+        for (int j = 1; j < UW; ++j) ck = j == k ? (float)rec[j].w : ck;
+        weigh(sub + k * GL, __builtin_bit_cast(uint32_t, ck));
+    }
+    for (int i = sub + UW * GL; i < pieces; i += GL) {
+        const f32x4 q = *(const f32x4*)(row + (int64_t)i * 16);
+        flt.eval(q, fs, fD);
+        if (fs >= -flt.tol_s && fD <= lim_D) weigh(i, __builtin_bit_cast(uint32_t, (float)q.w));
     }
     if (GL == 16) exact_stage<DPP_ROW_MIRROR>(D, best, c);
     if (GL >= 8) exact_stage<DPP_HALF_MIRROR>(D, best, c);
@@ -315,7 +339,7 @@ __device__ inline bool exact_step(const RowTab t, const char* row, int pieces, i
 // (own L2) takes runs of 16 consecutive blocks, the XCDs' runs side by side
 // (xcd_block, XCD_RUN_WALK).
 template <int MODE, int GL, bool FAR>
-__global__ __launch_bounds__(TRACE_BLOCK) void k_trace(
+__global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 5 : 1) void k_trace(
     const double* __restrict__ pos, const RowTab t, int64_t P, const int32_t* __restrict__ origins, int64_t n_origins,
     int64_t R, const double* __restrict__ dirs, int per_origin, int32_t* __restrict__ lens,
     const int64_t* __restrict__ ray_off, int32_t* __restrict__ ids, double* __restrict__ Zout, int64_t capacity,
@@ -413,16 +437,17 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(
         const int lim = pieces - sub;
         const uint64_t at0 = (FAR ? t.offset(code) : (uint64_t)(uint32_t)t.offset(code)) + (uint32_t)sub * 16;
         f32x4 rec[UW];
-        bool any[UW];
+        int cols = U0;  // pieces a lane of the wave's longest row
 #pragma unroll
         for (int i = 0; i < UW; ++i) {
             const bool has = (GL == 4 && i == 0) || i * GL < lim;  // every row has four pieces
-            any[i] = i < U0 || __builtin_amdgcn_ballot_w64(has);
-            if (any[i]) {
+            if (i < U0 || __builtin_amdgcn_ballot_w64(has)) {
                 const uint64_t at = has ? at0 : 0;
                 rec[i] = *(const f32x4*)(t.recs + (FAR ? at : (uint64_t)(uint32_t)at) + i * GL * 16);
+                if (i >= U0) cols = i + 1;
             }
         }
+        cols = __builtin_amdgcn_readfirstlane(cols);
         // the head, from the group's first two lanes (one quad each) or loaded again
         const u32x4 w0 = __builtin_bit_cast(u32x4, rec[0]);
         u32x4 hxy, hzi;
@@ -472,39 +497,38 @@ __global__ __launch_bounds__(TRACE_BLOCK) void k_trace(
         const float tol_s = __builtin_fmaf(A, 0x1p-21f, __builtin_fmaf(Rm, 0x1p-48f, t.floor_s));
         const float tol_D = __builtin_fmaf(10.f * A, tol_s, t.floor_D);
         const float inf = __builtin_inff();
-        float D1 = inf, D2 = inf;  // the lane's two least D, and the first's row code
+        // the lane's two least D among the candidates that may be forward, the first's row code and projection
+        float D1 = inf, D2 = inf, s1 = 0.f;
         uint32_t best = 0;
-        bool unsure = false;
         auto weigh = [&](const f32x4 q) {
             const float tx = px + q.x, ty = py + q.y, tz = pz + q.z;
             const float s = __builtin_fmaf(q.z, fz, __builtin_fmaf(q.y, fy, q.x * fx));
             const float T = __builtin_fmaf(tz, tz, __builtin_fmaf(ty, ty, tx * tx));
-            const float D = s > tol_s ? __builtin_fmaf(-s, s, T) : inf;
-            unsure = unsure || fabsf(s) <= tol_s;
+            const float D = s >= -tol_s ? __builtin_fmaf(-s, s, T) : inf;
             D2 = __builtin_amdgcn_fmed3f(D1, D2, D);
             const bool first = D < D1;
             D1 = first ? D : D1;
+            s1 = first ? s : s1;
             best = first ? __builtin_bit_cast(uint32_t, (float)q.w) : best;
         };
 #pragma unroll
         for (int i = 0; i < UW; ++i)
-            if (any[i]) weigh(rec[i]);
+            if (i < U0 || i < cols) weigh(rec[i]);
         if (__builtin_amdgcn_ballot_w64(UW * GL < lim))
             for (int i = UW * GL; i < lim; i += GL)  // rows longer than one pass
                 weigh(*(const f32x4*)(row + (int64_t)(sub + i) * 16));
-        D2 = unsure ? -inf : D2;
         const float least = group_reduce<GL>(D1, [](float a, float o) { return o < a ? o : a; });
+        if (least == inf) break;  // none may be forward: the ray leaves the model
         const float lim_D = least + tol_D;
-        const Filter flt = {px, py, pz, fx, fy, fz, tol_s};
-        // candidates that may be the rule's choice: one means it is known
+        // candidates that may be the rule's choice: one means it is known, if it is surely forward
         const bool mine = D1 <= lim_D;
-        const int rivals = group_reduce<GL>((mine ? 1 : 0) + (D2 <= lim_D ? 2 : 0), [](int a, int o) { return a + o; });
+        const int rivals = group_reduce<GL>((mine ? (s1 > tol_s ? 1 : 2) : 0) + (D2 <= lim_D ? 2 : 0),
+                                            [](int a, int o) { return a + o; });
         code = group_reduce<GL>(mine ? best : 0u, [](uint32_t a, uint32_t o) { return a > o ? a : o; });
-        if (rivals != 1) {
-            // none forward (D1 = D2 = inf in every lane): the ray leaves the model
-            if (least == inf && group_reduce<GL>(D2, [](float a, float o) { return o < a ? o : a; }) == inf) break;
-            if (!exact_step<GL>(t, row, pieces, sub, flt, lim_D, ox, oy, oz, dx, dy, dz, Z, code)) break;
-        }
+        const Filter flt = {px, py, pz, fx, fy, fz, tol_s, tol_D};
+        if (__builtin_expect(rivals != 1, 0) &&
+            !exact_step<GL, UW>(t, row, rec, cols, pieces, sub, flt, ox, oy, oz, dx, dy, dz, Z, code))
+            break;
     }
     if (MODE != TRACE_COUNT) {
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");

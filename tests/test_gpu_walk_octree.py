@@ -1,0 +1,64 @@
+"""The walk over an octree's leaves, where edges across the ray and equal distances leave the FP32
+filter undecided at one step in twenty: lists equal the oracle's bit for bit, in units that FP32 holds
+exactly and in others, whether a wave's rays share their direction (plans) or their origin (bare lists);
+and deciding such steps costs less than the rest of the walk."""
+import numpy as np
+import pytest
+
+import synth
+
+pytestmark = pytest.mark.gpu
+
+
+def _octree(**kw):
+    return synth.octree_model(seed=5, nblocks=1, nf_block=4, **kw)
+
+
+@pytest.mark.parametrize("units", ["dyadic", "thirds"])
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+def test_octree_lists(rt, orc, units, lanes):
+    import torch
+    m = _octree(lmin=2, lmax=5, target=1500)
+    if units == "thirds":
+        m.pos = m.pos * (1e15 / 3.0) + 1.234e14
+    model = rt.Model.from_numpy(m.pos, m.nbr_off, m.nbr_idx, m.vel)
+    ds = rt.DirSet.uniform(2)
+    _, dirs, _ = orc.dirset_uniform(2)
+    origins = np.arange(0, m.P, 3, dtype=np.int32)
+    org = torch.as_tensor(origins, device="cuda")
+    e = orc.trace_all(m, dirs, origins)
+    chi, eta, I_bc = (torch.as_tensor(x, dtype=torch.float64, device="cuda") for x in (m.chi, m.eta, m.I_bc))
+    J = torch.empty((len(origins), m.F), dtype=torch.float64, device="cuda")
+    plan = rt.Plan(model, ds, chi, eta, m.freq.len, m.freq.dx, I_bc, J, origins=org, precision=rt.RT_F64,
+                   schedule=rt.SCHED_SPATIAL, trace_lanes=lanes)
+    plan.run()
+    rt.sync_status()
+    for g in (plan.rays(), rt.trace(model, ds, origins=org)):
+        off, ids, Z = (x.cpu().numpy() for x in g)
+        assert np.array_equal(off, e[0])
+        assert np.array_equal(ids, e[1])
+        assert np.array_equal(Z.view(np.uint64), e[2].view(np.uint64))
+
+
+def test_octree_lists_cost(rt):
+    """Bare lists over the leaves take at most twice and a half the time of those over the same leaves with
+    their centres moved by a thousandth of the smallest cell, where no step is undecided."""
+    import torch
+    m = _octree(lmin=4, lmax=6, target=20000)
+    ds = rt.DirSet.uniform(2)
+    rng = np.random.default_rng(7)
+    t = []
+    for pos in (m.pos, m.pos + rng.uniform(-1e-3 / 64, 1e-3 / 64, m.pos.shape)):
+        model = rt.Model.from_numpy(pos, m.nbr_off, m.nbr_idx, m.vel)
+        cap = rt.trace(model, ds, n_origins=m.P)[1].numel()
+        best = np.inf
+        for _ in range(5):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            rt.trace_once(model, ds, cap, n_origins=m.P)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        t.append(best)
+    print("ms:", t)
+    assert t[0] <= 2.5 * t[1]
