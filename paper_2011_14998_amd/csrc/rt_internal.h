@@ -131,6 +131,7 @@ struct rt_model {
     uint32_t* codes = nullptr; // owned: each point's row code
     rt::RowTab tab;
     size_t row_bytes = 0;      // of recs
+    bool lattice = false;      // a sixteenth of the edges or more lie along an axis: an octree, a grid
     int device = -1;
     // host copy of the positions, made on first need (spatial orders of plans); the
     // positions may not change while the handle lives
@@ -149,7 +150,8 @@ hipError_t launch_check_model(const rt_model* m, int32_t* bad, uint64_t* reach, 
 // Layout of the rows of a model (tab.sh, tab.nb) and the bytes they take.
 size_t plan_rows(RowTab& tab, int64_t P, int64_t E);
 // Rows of a checked model, laid out in the point order `lay` (device [P], NULL: point
-// order), each in ascending key[id] (key NULL: ascending id); ws: build_rows_workspace(P) bytes.
+// order), each in ascending key[id] (key NULL: ascending id); ws: build_rows_workspace(P) bytes, whose
+// first 8 then hold the number of edges along an axis.
 size_t build_rows_workspace(int64_t P);
 hipError_t launch_build_rows(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s);
 // `order` (optional): spatially sorted permutation of origin positions; the

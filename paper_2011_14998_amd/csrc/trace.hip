@@ -72,12 +72,14 @@ __global__ __launch_bounds__(256) void k_layout_codes(const int64_t* __restrict_
 // id, or in ascending key[id] when a key is given (equal keys in list order).  The walk
 // relies on that order: equal distances go to the earlier record.  The row's last unit is
 // filled up with blank records.  The model has been checked, so every index is in range.
+// *axial: the edges along an axis.
 constexpr int BUILD_LANES = 16;
 
 __global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ pos, int64_t P,
                                                      const int64_t* __restrict__ off,
                                                      const int32_t* __restrict__ idx, const int32_t* __restrict__ key,
-                                                     const RowTab t, char* __restrict__ recs) {
+                                                     const RowTab t, char* __restrict__ recs,
+                                                     unsigned long long* __restrict__ axial) {
     const int64_t p = (blockIdx.x * (int64_t)blockDim.x + threadIdx.x) / BUILD_LANES;
     if (p >= P) return;  // whole groups leave together
     const int sub = threadIdx.x & (BUILD_LANES - 1);
@@ -88,6 +90,7 @@ __global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ p
     RowRec* rec = (RowRec*)(row + sizeof(RowHead)) + (counted ? 0 : 1);
     const double x = pos[3 * p], y = pos[3 * p + 1], z = pos[3 * p + 2];
     double longest = 0.0;
+    int along = 0;  // edges along an axis
     for (int j = sub; j < n; j += BUILD_LANES) {
         const int32_t k = idx[a + j];
         const int32_t kk = key ? key[k] : k;
@@ -102,6 +105,7 @@ __global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ p
         rec[rank] = RowRec{(float)ex, (float)ey, (float)ez, t.code[k]};
         const double l = sqrt(ex * ex + ey * ey + ez * ez);
         longest = l > longest ? l : longest;
+        along += (ex == 0.0) + (ey == 0.0) + (ez == 0.0) == 2;
     }
     const int filled = (int)(4 * row_units(n, t.nb)) - (counted ? 2 : 3);  // records that fit after rec[0]
     for (int j = n + sub; j < filled; j += BUILD_LANES) rec[j] = blank_rec();
@@ -109,8 +113,10 @@ __global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ p
     for (int o = BUILD_LANES / 2; o > 0; o >>= 1) {
         const double l = __shfl_xor(longest, o, BUILD_LANES);
         longest = l > longest ? l : longest;
+        along += __shfl_xor(along, o, BUILD_LANES);
     }
     if (sub == 0) {
+        if (along) atomicAdd(axial, (unsigned long long)along);
         // never below the longest edge
         *(RowHead*)row = RowHead{x, y, z, (int32_t)p, (float)(longest * 1.000001)};
         if (!counted) rec[-1] = blank_rec((uint32_t)n);
@@ -181,10 +187,12 @@ __global__ __launch_bounds__(256) void k_check_off(const int64_t* __restrict__ o
 // some before it issued the rest (7.9 ms).  50 000-point cloud, 96 pairs,
 // 2.6e8 steps: 5.6 ms (46e9 steps/s), against 9.4 ms with every candidate's
 // FP64 record (32 bytes) read and weighed; 26-neighbour grid, 5.0e8 steps: 10.0
-// ms against 16.4; 50 000 leaves of an octree, 4.1e8 steps: 10.7 against 15.1,
-// and bare lists of 20 000 of them at 24 pairs, whose waves mix directions, 4.2
-// against 4.25 (17.4 and 10.1 where any edge across the ray, however far its end,
-// sent the group to a rule that read its row again).
+// ms against 16.4; 50 000 leaves of an octree, 4.1e8 steps: 10.8 against 15.1,
+// and bare lists of 20 000 of them at 24 pairs 3.5 against 4.25 (17.4 and 10.1
+// where any edge across the ray, however far its end, sent the group to a rule
+// that read its row again).  Where nearly every step is undecided and few waves
+// hide the rounds to other rows' heads, it loses: lists of 512 points of a cubic
+// lattice 105 us against 91, walks at 16 lanes 10% longer.
 //
 // List entries are buffered across the group and written in blocks of RUNL =
 // max(GL, 8) entries aligned to absolute list positions (ids 32 or 64 bytes, Z
@@ -329,17 +337,21 @@ __device__ inline bool exact_step(const RowTab t, const char* row, const f32x4 (
     return best != INT32_MAX;
 }
 
-// Work order.  Without `order`, ray L is slot L (origin-major).  With `order`
+// Work order.  Without `order`, ray L is slot L (origin-major), but with TILE > 1
+// the origins are taken TILE at a time, direction-major among them: the rays of
+// a wave then share their direction.  With `order`
 // (a permutation of origin positions, spatially sorted) ray L is direction
 // L / n_origins of origin order[L % n_origins]: concurrent waves walk nearby
 // origins in the same direction and share most of the rows they read.  With
 // `ray_order` (n_rays origin positions, from k_length_order) ray L is direction
 // L / n_origins of origin ray_order[L]: the same windows of nearby origins,
-// their rays taken in order of length.  Blocks are renumbered so that each XCD
+// their rays taken in order of length.  Register bounds by lanes per ray: 8 lanes
+// at 6 waves per SIMD, 16 at 7 (graded cloud of 30k points 1.90 -> 1.79 and 2.82
+// -> 2.65 ms).  Blocks are renumbered so that each XCD
 // (own L2) takes runs of 16 consecutive blocks, the XCDs' runs side by side
 // (xcd_block, XCD_RUN_WALK).
-template <int MODE, int GL, bool FAR>
-__global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 5 : 1) void k_trace(
+template <int MODE, int GL, bool FAR, int TILE>
+__global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 5 : GL == 8 ? 6 : 7) void k_trace(
     const double* __restrict__ pos, const RowTab t, int64_t P, const int32_t* __restrict__ origins, int64_t n_origins,
     int64_t R, const double* __restrict__ dirs, int per_origin, int32_t* __restrict__ lens,
     const int64_t* __restrict__ ray_off, int32_t* __restrict__ ids, double* __restrict__ Zout, int64_t capacity,
@@ -375,6 +387,12 @@ __global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 5 : 1) void k_trace(
     } else {
         oi = L / two_r;
         rr = L - oi * two_r;
+        if (TILE > 1) {
+            const int64_t o0 = oi / TILE * TILE, j = L - o0 * two_r;
+            const int64_t m = n_origins - o0 < TILE ? n_origins - o0 : TILE;
+            rr = j / m;
+            oi = o0 + (j - rr * m);
+        }
     }
     const int64_t ray = oi * two_r + rr;
     const int64_t r = rr >> 1;
@@ -675,23 +693,24 @@ size_t plan_rows(RowTab& t, int64_t P, int64_t E) {
 }
 
 size_t build_rows_workspace(int64_t P) {
-    return al256(sizeof(int32_t) * (size_t)P) + al256(sizeof(int64_t) * (size_t)(P + 1)) + al256(scan_workspace(P));
+    return 256 + al256(sizeof(int32_t) * (size_t)P) + al256(sizeof(int64_t) * (size_t)(P + 1)) + al256(scan_workspace(P));
 }
 
 hipError_t launch_build_rows(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s) {
-    int32_t* units = (int32_t*)ws;
-    int64_t* start = (int64_t*)((char*)ws + al256(sizeof(int32_t) * (size_t)m->P));
+    int32_t* units = (int32_t*)((char*)ws + 256);
+    int64_t* start = (int64_t*)((char*)units + al256(sizeof(int32_t) * (size_t)m->P));
     void* scan_ws = (char*)start + al256(sizeof(int64_t) * (size_t)(m->P + 1));
     const unsigned g = (unsigned)blocks_for(m->P, 256);
     hipLaunchKernelGGL(k_layout_units, dim3(g), dim3(256), 0, s, m->off, lay, m->P, m->tab.sh, m->tab.nb,
                        units);
     hipError_t e = launch_scan(units, m->P, start, scan_ws, s);
+    if (e == hipSuccess) e = launch_fill_i32((int32_t*)ws, 2, 0, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_layout_codes, dim3(g), dim3(256), 0, s, start, m->off, lay, m->P, m->tab.nb,
                        (int64_t)(ROW_BLANK >> m->tab.sh), m->codes);
     hipLaunchKernelGGL(k_blank_rows, dim3(1), dim3(ROW_BLANK * 4), 0, s, (RowRec*)m->recs, ROW_BLANK * 4);
     hipLaunchKernelGGL(k_build_rows, dim3((unsigned)blocks_for(m->P * BUILD_LANES, 256)), dim3(256), 0, s, m->pos, m->P,
-                       m->off, m->idx, key, m->tab, m->recs);
+                       m->off, m->idx, key, m->tab, m->recs, (unsigned long long*)ws);
     return hipGetLastError();
 }
 
@@ -707,13 +726,18 @@ static hipError_t trace_launch(const rt_model* m, const int32_t* origins, int64_
     if (far) gl = 4;
     int32_t* ew = MODE == TRACE_COUNT ? nullptr : error_word();
     const dim3 grid(capped_blocks(blocks_for(n * gl, TRACE_BLOCK)));
-#define RT_TRACE(GL_, FAR_)                                                                                      \
-    hipLaunchKernelGGL((k_trace<MODE, GL_, FAR_>), grid, dim3(TRACE_BLOCK), 0, s, m->pos, m->tab, m->P, origins, \
+#define RT_TRACE(GL_, FAR_, TILE_)                                                                                    \
+    hipLaunchKernelGGL((k_trace<MODE, GL_, FAR_, TILE_>), grid, dim3(TRACE_BLOCK), 0, s, m->pos, m->tab, m->P, origins, \
                        n_origins, R, dirs, per_origin, lens, ray_off, ids, Z, capacity, ew, order, ray_order, num_xcds())
-    if (far) RT_TRACE(4, true);
-    else if (gl == 16) RT_TRACE(16, false);
-    else if (gl == 8) RT_TRACE(8, false);
-    else RT_TRACE(4, false);
+    // Bare lists over lattices: undecided steps depend on the direction first, so waves of 16 directions from
+    // one origin meet one at almost every step (ms, tiles of 1 and 16 origins: face-connected cubes of 55k
+    // points, 24 pairs 8.5 and 5.9, 26-neighbour grid 8.4 and 6.0, octree 4.2 and 3.5).  Irregular points have
+    // next to none, and near an origin its own rays share rows (log-spaced wind 3.4 and 3.8, disc 36.6 and 39.6).
+    if (far) RT_TRACE(4, true, 1);
+    else if (gl == 16) RT_TRACE(16, false, 1);
+    else if (gl == 8) RT_TRACE(8, false, 1);
+    else if (m->lattice && !order && !ray_order && !per_origin) RT_TRACE(4, false, MODE == TRACE_PADDED ? 1 : 16);
+    else RT_TRACE(4, false, 1);
 #undef RT_TRACE
     return hipGetLastError();
 }

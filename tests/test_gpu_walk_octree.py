@@ -1,7 +1,7 @@
 """The walk over an octree's leaves, where edges across the ray and equal distances leave the FP32
 filter undecided at one step in twenty: lists equal the oracle's bit for bit, in units that FP32 holds
-exactly and in others, whether a wave's rays share their direction (plans) or their origin (bare lists);
-and deciding such steps costs less than the rest of the walk."""
+exactly and in others, for plans and for bare lists, which take a lattice's origins in tiles of 16; and
+deciding such steps costs less than the rest of the walk."""
 import numpy as np
 import pytest
 
@@ -38,6 +38,22 @@ def test_octree_lists(rt, orc, units, lanes):
         assert np.array_equal(off, e[0])
         assert np.array_equal(ids, e[1])
         assert np.array_equal(Z.view(np.uint64), e[2].view(np.uint64))
+
+
+@pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
+def test_lattice_list_tiles(rt, orc, n):
+    """Bare lists around a tile of origins, in an order of their own."""
+    import torch
+    m = synth.lattice_model(5)
+    model = rt.Model.from_numpy(m.pos, m.nbr_off, m.nbr_idx, m.vel)
+    origins = np.random.default_rng(n).permutation(m.P)[:n].astype(np.int32)
+    _, dirs, _ = orc.dirset_uniform(2)
+    e = orc.trace_all(m, dirs, origins)
+    off, ids, Z = (x.cpu().numpy() for x in rt.trace(model, rt.DirSet.uniform(2),
+                                                      origins=torch.as_tensor(origins, device="cuda")))
+    assert np.array_equal(off, e[0])
+    assert np.array_equal(ids, e[1])
+    assert np.array_equal(Z.view(np.uint64), e[2].view(np.uint64))
 
 
 def test_octree_lists_cost(rt):
