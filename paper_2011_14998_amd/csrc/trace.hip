@@ -498,6 +498,7 @@ __global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 5 : GL == 8 ? 6 : 7) void k_
                 store_block((end & ~(int64_t)(RUNL - 1)) - RUNL, end < base + room ? end : base + room);
                 __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
                 __builtin_amdgcn_wave_barrier();
+                if (step > room) break;  // past its slot
             }
         }
         if (step >= (int32_t)P) break;  // Z grows at every step, so no ray is longer
