@@ -91,11 +91,18 @@ __global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ p
     const double x = pos[3 * p], y = pos[3 * p + 1], z = pos[3 * p + 2];
     double longest = 0.0;
     int along = 0;  // edges along an axis
+    bool sorted = true;  // a row given in order is placed as it is: a point may have every other as its neighbour
+    for (int j = sub; j + 1 < n; j += BUILD_LANES) {
+        const int32_t k = idx[a + j], l = idx[a + j + 1];
+        sorted = sorted && (key ? key[k] <= key[l] : k <= l);
+    }
+    const uint64_t group = (((uint64_t)1 << BUILD_LANES) - 1) << (threadIdx.x & 63 & ~(BUILD_LANES - 1));
+    sorted = (__builtin_amdgcn_ballot_w64(!sorted) & group) == 0;
     for (int j = sub; j < n; j += BUILD_LANES) {
         const int32_t k = idx[a + j];
         const int32_t kk = key ? key[k] : k;
-        int rank = 0;
-        for (int i = 0; i < n; ++i) {
+        int rank = sorted ? j : 0;
+        for (int i = 0; i < n && !sorted; ++i) {
             const int32_t o = idx[a + i];
             const int32_t ok = key ? key[o] : o;
             rank += (ok < kk) || (ok == kk && i < j);
