@@ -287,10 +287,11 @@ struct Filter {
 // The rule over the candidates that the filter leaves.  The whole wave waits for its undecided groups, so the
 // row's records are not read again: rec holds those of the first pass (cols per lane), and only the heads of
 // the candidates left, mostly one or two in a group, are loaded, a round for each that a lane has.
+// least: the least D of those surely forward where it is known (else infinite).
 template <int GL, int UW>
 __device__ inline bool exact_step(const RowTab t, const char* row, const f32x4 (&rec)[UW], int cols, int pieces,
-                                  int sub, const Filter flt, double ox, double oy, double oz, double dx, double dy,
-                                  double dz, double Zc, uint32_t& code) {
+                                  int sub, const Filter flt, float least, double ox, double oy, double oz, double dx,
+                                  double dy, double dz, double Zc, uint32_t& code) {
     double D = __builtin_inf();
     int best = INT32_MAX;
     uint32_t c = 0;
@@ -306,19 +307,22 @@ __device__ inline bool exact_step(const RowTab t, const char* row, const f32x4 (
             c = ck;
         }
     };
-    float least = __builtin_inff(), fs, fD, fDk[UW];  // the least D of those surely forward
+    float fs, fD, fDk[UW], sure = __builtin_inff();
 #pragma unroll
     for (int k = 0; k < UW; ++k)
         if (k < cols) {
             flt.eval(rec[k], fs, fD);
             fDk[k] = fs >= -flt.tol_s ? fD : NAN;
-            least = fs > flt.tol_s && fD < least ? fD : least;
+            sure = fs > flt.tol_s && fD < sure ? fD : sure;
         }
-    for (int i = sub + UW * GL; i < pieces; i += GL) {
-        flt.eval(*(const f32x4*)(row + (int64_t)i * 16), fs, fD);
-        least = fs > flt.tol_s && fD < least ? fD : least;
+    if (!(least < __builtin_inff())) {
+        for (int i = sub + UW * GL; i < pieces; i += GL) {
+            flt.eval(*(const f32x4*)(row + (int64_t)i * 16), fs, fD);
+            sure = fs > flt.tol_s && fD < sure ? fD : sure;
+        }
+        least = group_reduce<GL>(sure, [](float a, float o) { return o < a ? o : a; });
     }
-    const float lim_D = group_reduce<GL>(least, [](float a, float o) { return o < a ? o : a; }) + flt.tol_D;
+    const float lim_D = least + flt.tol_D;
     uint32_t left = 0;
 #pragma unroll
     for (int k = 0; k < UW; ++k)
@@ -546,14 +550,15 @@ __global__ __launch_bounds__(TRACE_BLOCK, GL == 4 ? 5 : GL == 8 ? 6 : 7) void k_
         const float least = group_reduce<GL>(D1, [](float a, float o) { return o < a ? o : a; });
         if (least == inf) break;  // none may be forward: the ray leaves the model
         const float lim_D = least + tol_D;
-        // candidates that may be the rule's choice: one means it is known, if it is surely forward
+        // candidates that may be the rule's choice, and (above 16 bits) those of them not surely forward: one
+        // that is surely forward is known to be it
         const bool mine = D1 <= lim_D;
-        const int rivals = group_reduce<GL>((mine ? (s1 > tol_s ? 1 : 2) : 0) + (D2 <= lim_D ? 2 : 0),
+        const int rivals = group_reduce<GL>((mine ? (s1 > tol_s ? 1 : 0x10001) : 0) + (D2 <= lim_D ? 2 : 0),
                                             [](int a, int o) { return a + o; });
         code = group_reduce<GL>(mine ? best : 0u, [](uint32_t a, uint32_t o) { return a > o ? a : o; });
         const Filter flt = {px, py, pz, fx, fy, fz, tol_s, tol_D};
         if (__builtin_expect(rivals != 1, 0) &&
-            !exact_step<GL, UW>(t, row, rec, cols, pieces, sub, flt, ox, oy, oz, dx, dy, dz, Z, code))
+            !exact_step<GL, UW>(t, row, rec, cols, pieces, sub, flt, rivals < 0x10000 ? least : inf, ox, oy, oz, dx, dy, dz, Z, code))
             break;
     }
     if (MODE != TRACE_COUNT) {

@@ -40,6 +40,34 @@ def test_octree_lists(rt, orc, units, lanes):
         assert np.array_equal(Z.view(np.uint64), e[2].view(np.uint64))
 
 
+@pytest.mark.parametrize("lanes", [4, 8, 16])
+def test_long_rows_of_ties(rt, orc, lanes):
+    """A lattice whose points are all neighbours of one another: undecided steps whose candidates lie past
+    the first pass over a row, those that tie and those across the ray."""
+    import torch
+    m = synth.lattice_model(5)
+    a, b = np.triu_indices(m.P, 1)
+    off, idx = synth.models.csr_from_edges(m.P, a, b)
+    model = rt.Model.from_numpy(m.pos, off, idx, None)
+    full = synth.Model("full", m.pos, off, idx, None, m.chi, m.eta, m.freq, m.I_bc)
+    origins = np.arange(0, m.P, 7, dtype=np.int32)
+    org = torch.as_tensor(origins, device="cuda")
+    _, dirs, _ = orc.dirset_uniform(2)
+    e = orc.trace_all(full, dirs, origins)
+    chi, eta, I_bc = (torch.as_tensor(x, dtype=torch.float64, device="cuda") for x in (m.chi, m.eta, m.I_bc))
+    J = torch.empty((len(origins), m.F), dtype=torch.float64, device="cuda")
+    ds = rt.DirSet.uniform(2)
+    plan = rt.Plan(model, ds, chi, eta, m.freq.len, m.freq.dx, I_bc, J, origins=org, precision=rt.RT_F64,
+                   trace_lanes=lanes)
+    plan.run()
+    rt.sync_status()
+    for g in (plan.rays(), rt.trace(model, ds, origins=org)):
+        got = [x.cpu().numpy() for x in g]
+        assert np.array_equal(got[0], e[0])
+        assert np.array_equal(got[1], e[1])
+        assert np.array_equal(got[2].view(np.uint64), e[2].view(np.uint64))
+
+
 @pytest.mark.parametrize("n", [1, 15, 16, 17, 33])
 def test_lattice_list_tiles(rt, orc, n):
     """Bare lists around a tile of origins, in an order of their own."""
