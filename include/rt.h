@@ -225,7 +225,8 @@ typedef struct {
     int32_t bins_per_octave;  /* RT_SCHED_BINNED bin edges: a pair whose line holds N points goes to bin
                                  floor(bins_per_octave * log2 N) (the last bin open-ended); 1, 2, 4 or
                                  8 (0 = 4, quarter octaves) */
-    int32_t group;            /* sweep: line points whose loads are issued together, 4 or 8 (0 = 4) */
+    int32_t group;            /* sweep: line points whose loads are issued together, 4 or 8 (0 = 4); launches of many
+                                 second-order lines, which the library sweeps several to a wave, have no groups */
     int32_t trace_lanes;      /* plans: lanes walking one ray, 4, 8 or 16 (0 = 4) */
     int64_t padded_trace_budget; /* plans, RT_WALK_PADDED: bytes allowed for single-pass tracing into
                                     padded per-ray slots (longest ray x 12 bytes per ray); 0 = 32 GiB;

@@ -315,6 +315,7 @@ extern "C" rt_status rt_compute_J(const rt_model* m, const rt_dirset* set_, cons
         SolveLaunch a = base;
         a.origins = org_c;
         a.n_origins = c;
+        plan_lines(a, o.precision);  // for the chunk's lines (either sweep gives the same bits)
         a.dirs = dirs_c;
         a.w2 = w2_c;
         a.ray_off = off;

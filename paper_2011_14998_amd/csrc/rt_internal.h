@@ -227,6 +227,7 @@ struct SolveLaunch {
     // several lines per wave (plan_lines): frequencies per lane (0: not applicable), lanes per line, lines
     // per wave, chunks of 64 lanes per line; moving media: padded tables (nullptr: none) and their row length
     int vpl, lpl, lines, line_chunks;
+    double lines_gain;     // what it is expected to save of the one-line sweep's time (a fraction)
     int pad_ld;
     void* pad_chi;
     void* pad_eta;

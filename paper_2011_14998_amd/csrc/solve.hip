@@ -777,6 +777,7 @@ __device__ inline void sweep(const ItemCtx& c, int64_t base, int n, const LaneFr
                     if (SCH == 0 || done > 0) {
                         const T dt = (c_prev + cc) * ds_prev;  // ds_prev holds ds times half_step
                         row_s<T, SCH>(st, done == 1, dt, c_prev, e_prev, cc, et, I);
+                        if (SCH == 0 && sizeof(T) == 8 && !UDX) __builtin_amdgcn_sched_barrier(0);  // see solve_direct_waves
                     }
                     c_prev = cc;
                     e_prev = et;
@@ -903,6 +904,7 @@ __device__ inline void sweep_half(const ItemCtx& c, double nx, double ny, double
                         et = ea[g];
                     }
                     row2<T>(st, (c_prev + cc) * ds_prev, c_prev, e_prev);
+                    if (sizeof(T) == 4 || !UDX) __builtin_amdgcn_sched_barrier(0);  // see solve_direct_waves
                     c_prev = cc;
                     e_prev = et;
                     ds_prev = dsv[g];
@@ -1040,16 +1042,18 @@ __device__ inline void solve_item(const SolveLaunch& a, int64_t w, int nfc, int 
     }
 }
 
-// Waves per SIMD the direct sweep is compiled for: the FP32 second-order sweep with
-// load groups of 4 and one frequency spacing fits 64 VGPRs (one spilled register), so
-// 8 waves share a SIMD and hide more of the table loads' latency (on the 64-cloud batch
-// 396 ms against 407 at the 7 waves its registers would otherwise allow); its packed
-// half-wave variant fits 80 (6 waves, two spilled; the 507k-leaf octree 747 ms against
-// 762 with groups of 8 at 4 waves).  The refined sweeps take the bounds below; the
-// others keep the compiler's choice (held to 64 registers they spill heavily).
-template <typename T, bool UDX, int GROUP, int REF, int SCH, bool PACK>
+// Waves per SIMD the direct sweep is compiled for.  The FP32 second-order sweep with load groups of 4 and one
+// frequency spacing takes 7 for moving media (72 VGPRs, none spilled; at 8 four are: 64 frequencies, 120k lines
+// 294 -> 279 us) and 8 for static ones; its packed half-wave variant 6 (80 VGPRs; at 5 waves 6% slower).  In FP64 4 for moving media (5 and 6 for
+// static ones, packed and not): the compiler's own choice gives a wave away (packed, 96 frequencies 1149 -> 1048 us).
+// With several spacings in FP64, and in the packed FP32 variant, the points' interpolations stay out of the row before
+// them (sched_barrier): hoisted, they cost the registers that the bounds leave (645 -> 624 and 2107 -> 2068 us).  The refined sweeps take the bounds
+// below; the others keep the compiler's choice (held to 64 registers they spill heavily).
+template <typename T, bool MOVING, bool UDX, int GROUP, int REF, int SCH, bool PACK>
 constexpr int solve_direct_waves() {
-    if (!UDX || GROUP != 4) return 1;
+    if (GROUP != 4) return 1;
+    if (sizeof(T) == 8 && REF == 0 && SCH == 0) return MOVING ? 4 : PACK ? 5 : 6;
+    if (!UDX) return 1;
     // refined lines with both refinements (measured on the 50k wind at dtau_max = 1): FP32 second-order rows
     // at 5 waves (39.7 -> 38.6 ms; 6 waves 47.1), fourth-order at 4 (70.8 -> 59.6 ms), FP64 at 3 (78.9 -> 59.1
     // and 113.5 -> 94.2 ms); the plain FP64 sweep keeps the compiler's choice (43.3 ms against 44.4 at 5 waves)
@@ -1059,11 +1063,11 @@ constexpr int solve_direct_waves() {
     // fourth-order at 5 waves 4.39 and 3.11 (4: 4.59, 3.29), FP64 at 4 waves 5.78 and 2.24, fourth-order 6.79
     // and 4.74 (3: 5.88, 2.40, 7.21, 5.07)
     if (REF) return sizeof(T) == 4 ? (SCH == 0 ? 6 : 5) : 4;
-    return (sizeof(T) == 4 && SCH == 0) ? (PACK ? 6 : 8) : 1;
+    return (sizeof(T) == 4 && SCH == 0) ? (PACK ? 6 : MOVING ? 7 : 8) : 1;
 }
 
 template <typename T, bool MOVING, bool UDX, int GROUP, int REF, int SCH, bool PACK>
-__global__ __launch_bounds__(SOLVE_BLOCK, (solve_direct_waves<T, UDX, GROUP, REF, SCH, PACK>())) void k_solve_direct(
+__global__ __launch_bounds__(SOLVE_BLOCK, (solve_direct_waves<T, MOVING, UDX, GROUP, REF, SCH, PACK>())) void k_solve_direct(
     const SolveLaunch a) {
     constexpr int WORDS = REF != 0 ? REF_STAGE_WORDS : STAGE_WORDS;
     __shared__ uint32_t stage_all[WAVES_PER_BLOCK * 64 * WORDS];
@@ -1556,12 +1560,15 @@ __global__ __launch_bounds__(SOLVE_BLOCK, 4) void k_solve_lines(const SolveLaunc
         solve_lines<T, V, MOVING, UDX>(a, live, oi, r, l, lds);
     };
     if (PERSIST) {
+        // as many lines' work per atomic as the one-line sweep takes
+        const int64_t share = PERSIST_CHUNK * units / (n_pairs * nfc);
+        const int take = share > 1 ? (int)share : 1;
         for (;;) {
             int it0 = 0;
-            if (lane == 0) it0 = atomicAdd(a.queue, PERSIST_CHUNK);
+            if (lane == 0) it0 = atomicAdd(a.queue, take);
             it0 = __builtin_amdgcn_readfirstlane(it0);
             if ((int64_t)it0 >= units) break;
-            const int64_t end = (int64_t)it0 + PERSIST_CHUNK < units ? (int64_t)it0 + PERSIST_CHUNK : units;
+            const int64_t end = (int64_t)it0 + take < units ? (int64_t)it0 + take : units;
             for (int64_t w = it0; w < end; ++w) unit(w);
         }
     } else {
@@ -1764,15 +1771,30 @@ static void solve_dispatch(const SolveLaunch& a, bool persist, dim3 grid, hipStr
 }
 
 // Values per lane of the multi-line sweep for this launch's frequencies, lanes per line, lines per wave and
-// chunks of 64 lanes per line; false when it does not apply.
+// chunks of 64 lanes per line, and whether it is the faster sweep for this launch: a.vpl, 0 where it does not
+// apply or is not.
+//
+// Its waves are fewer and each of its points takes longer, so it is faster where the one-line sweep's waves
+// more than fill the chip and most of its lanes would idle or its FP64 pipes wait; a launch of few lines is bound by
+// the time of one wave.  Measured on clouds of 1200 to 20 000 points (one line per wave against this, at U waves of
+// the one-line sweep), time = (ratio + X / U) times the one-line sweep's:
+//   ratio  VALU work per wave, 15 V + 14 instructions against 22 (FP32), 26.5 (FP64) and 32 (FP64, moving), with
+//          8.5% per further line of the wave for the longest of its lines; one lane per line, and two in FP32,
+//          stage too few points at a time (doubled, half as much again).  31 frequencies 0.67 in FP32 and 0.52 in
+//          FP64 (measured 0.7 and 0.55), 96 0.73 (0.70), 200 0.84 (0.83), 64 in FP64 0.90 (0.89).
+//   X      2000 + 450 lines in FP32, 4000 + 500 lines with the padded copies of moving media, 1500 + 350 lines in FP64.
+// Static, FP32, 16 frequencies: U = 6000 11.6 us against 17.3, 24 000 25.4 against 19.5; FP64, 31 frequencies: 600 8.9
+// against 11.7, 7200 19.4 against 14.3.  With every lane of a one-line wave busy (60 to 64 frequencies in FP32) the
+// two are equal at half a million waves and this one is up to 4% faster beyond (wind 11.8 -> 11.7 ms).
 bool plan_lines(SolveLaunch& a, int precision) {
     a.vpl = 0;
+    a.lines_gain = 0.0;
     if (a.scheme != RT_SCHEME_FEAUTRIER2 || a.dtau_max_rcp > 0.0 || a.dv_max_rcp > 0.0) return false;
-    const bool moving = a.vel != nullptr;
-    const size_t es = precision == RT_F64 ? 8 : 4;
+    const bool moving = a.vel != nullptr, f64 = precision == RT_F64;
+    const size_t es = f64 ? 8 : 4;
     double best = 0.0;
     for (int V : {4, 3, 2}) {
-        if ((V == 2) != (precision == RT_F64)) continue;
+        if ((V == 2) != f64) continue;
         int lanes = 0, ld = 0;
         if (moving) {
             for (int b = 0; b < a.n_blocks; ++b) {
@@ -1801,6 +1823,16 @@ bool plan_lines(SolveLaunch& a, int precision) {
             a.pad_ld = ld;
         }
     }
+    if (!a.vpl) return false;
+    const double U = (double)solve_items(a), SIMDS = 4.0 * num_cus() / 1024.0;  // X is for 1024 SIMDs
+    const double one = (f64 ? moving ? 32.0 : 26.5 : 22.0) * ((a.F + 63) / 64);
+    double ratio = (15.0 * a.vpl + 14.0) * a.line_chunks / a.lines * (1.0 + 0.085 * (a.lines - 1)) / one;
+    if (a.lpl == 1) ratio *= 2.0;
+    if (a.lpl == 2 && !f64) ratio *= 1.5;
+    const double X = f64 ? 1500.0 + 350.0 * a.lines : moving ? 4000.0 + 500.0 * a.lines : 2000.0 + 450.0 * a.lines;
+    a.lines_gain = 1.0 - ratio;
+    if (!f64 && U >= 524288.0 * SIMDS) a.lines_gain = a.lines_gain > 0.04 ? a.lines_gain : 0.04;
+    if (a.lines_gain * U < X * SIMDS) a.vpl = 0;
     return a.vpl != 0;
 }
 
