@@ -1025,7 +1025,7 @@ static hipError_t plan_pair_orders(rt_plan* p) {
     if (ws) (void)hipFree(ws);
     if (e != hipSuccess) {
         if (out) (void)hipFree(out);
-        if (e == hipErrorOutOfMemory) {  // an optimisation only: the sweep keeps the Morton order
+        if (e == hipErrorOutOfMemory && !p->pad) {  // an optimisation only: the sweep keeps the Morton order
             (void)hipGetLastError();
             return hipSuccess;
         }
@@ -1035,7 +1035,13 @@ static hipError_t plan_pair_orders(rt_plan* p) {
     return hipSuccess;
 }
 
-static rt_status plan_configure(rt_plan* p, const rt_solve_opts& o) {
+// (short_of_memory: whether that is why it failed)
+static rt_status plan_try_configure(rt_plan* p, const rt_solve_opts& o, bool& short_of_memory) {
+    const auto hip_fail = [&](hipError_t e, const char* what) {
+        short_of_memory = e == hipErrorOutOfMemory;
+        return ::hip_fail(e, what);
+    };
+    short_of_memory = false;
     if (o.schedule < RT_SCHED_DIRECT || o.schedule > RT_SCHED_SPATIAL) return fail(RT_ERR_ARG, "plan: bad schedule");
     if (o.group != 0 && o.group != 4 && o.group != 8) return fail(RT_ERR_ARG, "plan: group must be 4 or 8");
     if (o.trace_lanes != 0 && o.trace_lanes != 4 && o.trace_lanes != 8 && o.trace_lanes != 16)
@@ -1124,6 +1130,20 @@ static rt_status plan_configure(rt_plan* p, const rt_solve_opts& o) {
     if (e != hipSuccess) return hip_fail(e, "plan: graph capture");
     ++p->version;
     return RT_OK;
+}
+
+// Applies the options; the padded tables, which a plan can do without, give way to memory that they need (also
+// to the pair orders, worth more than they are).
+static rt_status plan_configure(rt_plan* p, const rt_solve_opts& o) {
+    bool short_of_memory;
+    rt_status st = plan_try_configure(p, o, short_of_memory);
+    if (st && short_of_memory && p->pad) {
+        (void)hipGetLastError();
+        (void)hipFree(p->pad);  // waits for the device
+        p->pad = p->base.pad_chi = p->base.pad_eta = p->a.pad_chi = p->a.pad_eta = nullptr;
+        st = plan_try_configure(p, o, short_of_memory);
+    }
+    return st;
 }
 
 hipError_t rt::plan_enqueue_step(rt_plan* p, hipStream_t s) { return plan_enqueue(p, s); }
@@ -1257,12 +1277,6 @@ rt_status rt::plan_create_ordered(const rt_model* m, rt_dirset* set, const int32
     p->base = p->a;
     p->stream = s;
     st = plan_configure(p, p->o);
-    if (st && p->pad) {  // perhaps the copies took the memory it needed
-        (void)hipGetLastError();
-        (void)hipFree(p->pad);
-        p->pad = p->base.pad_chi = p->base.pad_eta = nullptr;
-        st = plan_configure(p, p->o);
-    }
     if (st) {
         plan_free(p);
         return st;
