@@ -300,7 +300,8 @@ extern "C" rt_status rt_model_create(const double* pos, int64_t P, const int64_t
 }
 
 rt_status rt::model_create(const double* pos, int64_t P, const int64_t* nbr_off, const int32_t* nbr_idx, int64_t E,
-                           const float* vel, const int32_t* key, bool morton_rows, hipStream_t s, rt_model** out) {
+                           const float* vel, const int32_t* key, bool morton_rows, hipStream_t s, rt_model** out,
+                           int row_layout) {
     if (!out) return fail(RT_ERR_ARG, "rt_model_create: NULL output");
     *out = nullptr;
     if (!pos || !nbr_off || (E > 0 && !nbr_idx) || P <= 0 || E < 0)
@@ -315,7 +316,8 @@ rt_status rt::model_create(const double* pos, int64_t P, const int64_t* nbr_off,
     m->E = E;
     m->vel = vel;
     RT_HIP(hipGetDevice(&m->device));
-    m->row_bytes = plan_rows(m->tab, P, E);
+    m->row_bytes = plan_rows(m->tab, P, E, row_layout);
+    m->far = row_layout != ROWS_BY_SIZE || m->row_bytes > 0xFFFFFFFFull;
     int32_t* chk = nullptr;  // {bad bits, -, reach (64 bits)}
     hipError_t e = hipMalloc((void**)&m->recs, m->row_bytes);
     if (e == hipSuccess) e = hipMalloc((void**)&m->codes, sizeof(uint32_t) * (size_t)P);

@@ -131,6 +131,7 @@ struct rt_model {
     uint32_t* codes = nullptr; // owned: each point's row code
     rt::RowTab tab;
     size_t row_bytes = 0;      // of recs
+    bool far = false;          // beyond 32-bit offsets
     bool lattice = false;      // a sixteenth of the edges or more lie along an axis: an octree, a grid
     int device = -1;
     // host copy of the positions, made on first need (spatial orders of plans); the
@@ -147,8 +148,11 @@ namespace rt {
 // 4 self neighbour, 8 position not finite or beyond 1e150); *reach: the bits of the largest
 // |coordinate| (both zeroed by the caller).
 hipError_t launch_check_model(const rt_model* m, int32_t* bad, uint64_t* reach, hipStream_t s);
-// Layout of the rows of a model (tab.sh, tab.nb) and the bytes they take.
-size_t plan_rows(RowTab& tab, int64_t P, int64_t E);
+// Layout of the rows of a model (tab.sh, tab.nb) and the bytes they take.  ROWS_BY_SIZE takes what the size needs;
+// the others force what large models take: rows addressed by 64-bit offsets (FAR), and besides without a row's
+// units in its code (WIDE).
+enum RowLayout { ROWS_BY_SIZE = 0, ROWS_FAR = 1, ROWS_WIDE = 2 };
+size_t plan_rows(RowTab& tab, int64_t P, int64_t E, int layout);
 // Rows of a checked model, laid out in the point order `lay` (device [P], NULL: point
 // order), each in ascending key[id] (key NULL: ascending id); ws: build_rows_workspace(P) bytes, whose
 // first 8 then hold the number of edges along an axis.
@@ -282,7 +286,8 @@ void morton_order_host(const double* pos, int64_t P, const int32_t* origins, int
 // morton_rows: lay the rows of the records out in the Morton order of the points (else in
 // point order, for points that are already so ordered).
 rt_status model_create(const double* pos, int64_t P, const int64_t* nbr_off, const int32_t* nbr_idx, int64_t E,
-                       const float* vel, const int32_t* key, bool morton_rows, hipStream_t s, rt_model** out);
+                       const float* vel, const int32_t* key, bool morton_rows, hipStream_t s, rt_model** out,
+                       int row_layout = ROWS_BY_SIZE);
 // Plans: create with a given origin order (nullptr = Morton order of the origins), enqueue the
 // whole step on a stream (what the plan's graph holds), and a counter that changes whenever the
 // plan's graph is re-captured.

@@ -697,9 +697,9 @@ static size_t al256(size_t v) { return (v + 255) / 256 * 256; }
 // number of units.  28 bits of start and units of 64 bytes reach 17 GB of rows, far beyond
 // any model measured; larger models give up the four bits (every row holds its degree) and
 // take units of 128 bytes, which reach every model the ABI accepts.
-size_t plan_rows(RowTab& t, int64_t P, int64_t E) {
+size_t plan_rows(RowTab& t, int64_t P, int64_t E, int layout) {
     const int64_t units = ROW_BLANK + 2 * P + E / 4;  // of 64 bytes, at most
-    const bool wide = units >= (int64_t)1 << 28;
+    const bool wide = layout == ROWS_WIDE || units >= (int64_t)1 << 28;
     t.nb = wide ? 0 : 4;
     t.sh = wide ? 1 : 0;
     return (size_t)(units + (wide ? P : 0)) * 64;
@@ -735,8 +735,7 @@ static hipError_t trace_launch(const rt_model* m, const int32_t* origins, int64_
     const int64_t n = n_origins * 2 * R;
     if (n == 0) return hipSuccess;
     if (gl != 8 && gl != 16) gl = 4;  // 0 and other values: the default, 4 lanes
-    const bool far = m->row_bytes > 0xFFFFFFFFull;  // rows beyond 32-bit offsets: 4 lanes
-    if (far) gl = 4;
+    if (m->far) gl = 4;
     int32_t* ew = MODE == TRACE_COUNT ? nullptr : error_word();
     const dim3 grid(capped_blocks(blocks_for(n * gl, TRACE_BLOCK)));
 #define RT_TRACE(GL_, FAR_, TILE_)                                                                                    \
@@ -746,7 +745,7 @@ static hipError_t trace_launch(const rt_model* m, const int32_t* origins, int64_
     // one origin meet one at almost every step (ms, tiles of 1 and 16 origins: face-connected cubes of 55k
     // points, 24 pairs 8.5 and 5.9, 26-neighbour grid 8.4 and 6.0, octree 4.2 and 3.5).  Irregular points have
     // next to none, and near an origin its own rays share rows (log-spaced wind 3.4 and 3.8, disc 36.6 and 39.6).
-    if (far) RT_TRACE(4, true, 1);
+    if (m->far) RT_TRACE(4, true, 1);
     else if (gl == 16) RT_TRACE(16, false, 1);
     else if (gl == 8) RT_TRACE(8, false, 1);
     else if (m->lattice && !order && !ray_order && !per_origin) RT_TRACE(4, false, MODE == TRACE_PADDED ? 1 : 16);
