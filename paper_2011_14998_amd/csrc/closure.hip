@@ -1066,7 +1066,11 @@ __global__ __launch_bounds__(256) void k_train_step(const float* __restrict__ bp
 // formed once per point of the workgroup, the logarithms of the first LOG_CACHE
 // neighbours are kept in LDS for the second pass over them, and a row goes out
 // as four 16-byte stores where feat is aligned (WIDE).  65536 points of 15
-// neighbours at 64 frequencies with 6 pairs: 384 -> 285 us.
+// neighbours at 64 frequencies with 6 pairs: 384 -> 283 us, at 31 frequencies 187
+// -> 159.  The distances come first, so calls too small to hide their latency pay
+// for it: summed by lane reads and in unrolled loads, 1000 points of 16
+// frequencies take 17.0 us (18.4 by shuffles, 16.8 in one loop with the rest);
+// unrolled by 8 the kernel loses two waves per SIMD.
 constexpr int LOG_CACHE = 20;  // 20 KB of LDS: seven workgroups per CU; a mesh point has 15 neighbours on average
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_features(const double* __restrict__ pos, const int64_t* __restrict__ off,
@@ -1098,9 +1102,13 @@ __global__ __launch_bounds__(256) void k_features(const double* __restrict__ pos
             const int64_t e0 = off[p], e1 = off[p + 1];
             double L = 0.0;
             for (int64_t e = e0; e < e1; e += 64) {
-                const int m = (int)(e1 - e < 64 ? e1 - e : 64);
+                const int m = __builtin_amdgcn_readfirstlane((int)(e1 - e < 64 ? e1 - e : 64));
                 const double d = (t & 63) < m ? dist(p, e + (t & 63)) : 0.0;
-                for (int l = 0; l < m; ++l) L += __shfl(d, l, 64);
+                for (int l = 0; l < m; ++l) {
+                    const int2 h = __builtin_bit_cast(int2, d);
+                    L += __builtin_bit_cast(double, make_int2(__builtin_amdgcn_readlane(h.x, l),
+                                                              __builtin_amdgcn_readlane(h.y, l)));
+                }
             }
             if ((t & 63) == 0) sL[c] = (float)(L / (double)(e1 - e0));
         }
@@ -1109,6 +1117,7 @@ __global__ __launch_bounds__(256) void k_features(const double* __restrict__ pos
         if (p >= 0) {
             const int64_t e0 = off[p], e1 = off[p + 1];
             double L = 0.0;
+#pragma unroll 4
             for (int64_t e = e0; e < e1; ++e) L += dist(p, e);
             sL[t] = (float)(L / (double)(e1 - e0));
         }
