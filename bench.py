@@ -51,7 +51,7 @@ TUNED = {
 
 
 SCHEDULE_NAMES = {0: "direct launch in slot order", 1: "length-binned persistent launch",
-                  2: "direct launch direction by direction over Morton-ordered origins, XCD runs of 16 (walk) and 64 (sweep) workgroups"}
+                  2: "direct launch direction by direction over Morton-ordered origins, XCD runs of 16 (walk) and 64 (sweep of several lines per wave; 256 of one) workgroups"}
 
 
 def _log(msg):

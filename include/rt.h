@@ -112,11 +112,12 @@ rt_status rt_dirset_destroy(rt_dirset* set);
  * Then builds a table of rows (per point 32 bytes and per neighbour entry 16:
  * the edge to it and where its own row lies, each row sorted by id, rounded up
  * to whole units of 64 bytes) that the tracer reads instead of chasing nbr_idx
- * into pos and nbr_off, with the rows laid out in the Morton order of the points (computed on the host from a copy of the
- * positions, which the handle keeps for the spatial orders of plans; 24 bytes
- * of host memory per point).  The order of a point's neighbours in nbr_idx and
- * the order of the points do not affect any result.  The positions and lists
- * must not change while the handle lives. */
+ * into pos and nbr_off, with the rows laid out in the Morton order of the
+ * points (computed on the host from a copy of the positions, which the handle
+ * keeps for the spatial orders of plans; 24 bytes of host memory per point).
+ * The order of a point's neighbours in nbr_idx and the order of the points do
+ * not affect any result.  The positions and lists must not change while the
+ * handle lives. */
 rt_status rt_model_create(const double* pos, int64_t P, const int64_t* nbr_off, const int32_t* nbr_idx,
                           int64_t E, const float* vel, void* stream, rt_model** out);
 rt_status rt_model_destroy(rt_model* model);
@@ -190,10 +191,10 @@ rt_status rt_trace(const rt_model* model, const rt_dirset* set, const int32_t* o
  * precision RT_F64: all FP64 (tables must be RT_F64).  RT_F32: tables RT_F32,
  * sweep in FP32; ds is always formed in FP64 from the FP64 Z.  The rows are
  * carried per unit inner step (F = dtau G, Z = dtau Y), so the only
- * elimination coefficient, (dtau_{d-1} + dtau_d)/2, is in FP32 exactly its FP64
- * value rounded once: every row, however small its steps, has FP64
- * coefficients, and no row needs a separate FP64 path (so there is no
- * threshold option for one). */
+ * elimination coefficient, (dtau_{d-1} + dtau_d)/2, is a sum of the steps and
+ * in FP32 within a rounding or two of its FP64 value: every row, however small
+ * its steps, has accurate coefficients, and no row needs a separate FP64 path
+ * (so there is no threshold option for one). */
 typedef struct {
     int32_t n_blocks;
     const int32_t* len; /* host [n_blocks] */
@@ -212,7 +213,8 @@ typedef struct {
                                  queue, longest lines first, 16 items per queue atomic (plans: the
                                  origins' Morton order inside each bin); RT_SCHED_SPATIAL (plans only): sweep items
                                  direction by direction, each XCD taking runs of 256 consecutive
-                                 workgroups (the XCDs' runs side by side), with a uniform
+                                 workgroups (64 where a wave sweeps several lines; the XCDs' runs
+                                 side by side), with a uniform
                                  set each pair's items in that pair's line order (origins sorted by the
                                  2D Morton code of their position across the pair's direction, then
                                  along it; built on the device when the plan is configured, R x

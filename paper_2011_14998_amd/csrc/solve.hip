@@ -24,17 +24,17 @@
 //     G_d = (a+b)/2 + G_{d-1} r_{d-1},   r_d = 1/(1 + b G_d),
 //     Y_d = ((a+b)/2 S_d + Y_{d-1}) r_d,
 //     G_0 = 1 + b/2,  Y_0 = (b/2 S_0 + I) r_0.
-// One reciprocal per row, and the only coefficient, (a+b)/2, is the correctly
-// rounded exact value in any precision (an FP32 evaluation equals the FP64
-// one rounded once), however small the steps.  Every term is a sum or product
-// of positive numbers, so small optical-depth steps lose nothing to
-// cancellation.  At the origin (a, b the steps to the two sides' last rows)
+// One reciprocal per row, and the only coefficient, (a+b)/2, is a sum: in any
+// precision within a rounding or two of its exact value, however small the
+// steps.  Every term is a sum or product of positive numbers, so small
+// optical-depth steps lose nothing to cancellation.  At the origin (a, b the steps to the two sides' last rows)
 //     u = ((a+b)/2 S + Y_- + Y_+) / ((a+b)/2 + G_- r_- + G_+ r_+),
 // and a side without points counts as a = 0, G = r = 1, Y = I.
 //
 // As computed (Row2): steps are carried divided by sqrt 2 and G and Y times
 // sqrt 2, which leaves every formula above as it is but for (a+b)/2, now a + b,
-// and G = r = 1, Y = I before the far end, now G = sqrt 2, Y = sqrt 2 I.  With S_d
+// and G = r = 1, Y = I before the far end, now G = sqrt 2, Y = sqrt 2 I (the two
+// constants' rounding enters; errors against 64 bits measure the same).  With S_d
 // = e/c the row's two quotients share the reciprocal q = 1/(D c), D = 1 + b G:
 //     r = q c,  Y = h (q e) + r Y_{d-1},  h = a + b:
 // ten operations and one reciprocal.  A line starts from that state with c = 1,
@@ -42,10 +42,10 @@
 // takes the same row, the first included.
 //
 // Per-point data that is the same for every frequency (point id, ds, the
-// velocity projection) is loaded for 64 points at once, one per lane, and
-// broadcast with readlane; each lane then gathers its own chi/eta values of
-// that point's row -- 64 consecutive values, one coalesced 256-byte read per
-// table for FP32.
+// velocity projection) is loaded for 64 points at once, one per lane, and staged
+// in LDS; each lane then gathers its own chi/eta values of that point's row -- 64
+// consecutive values, one coalesced 256-byte read per table for FP32.  Launches
+// of many second-order lines take several of them per wave instead (below).
 #include "rt_internal.h"
 
 #include <type_traits>
@@ -1580,7 +1580,7 @@ __global__ __launch_bounds__(SOLVE_BLOCK, 4) void k_solve_lines(const SolveLaunc
     }
 }
 
-// Padded copies of the tables (see sweep_lines): row p holds, block after block, V copies of the
+// Padded copies of the tables (see "several lines per wave"): row p holds, block after block, V copies of the
 // block's first value, its values, V copies of its last.
 template <typename T>
 __global__ __launch_bounds__(256) void k_pad_tables(const SolveLaunch a, int V, T* __restrict__ pc, T* __restrict__ pe) {
@@ -1836,8 +1836,8 @@ bool plan_lines(SolveLaunch& a, int precision) {
     return a.vpl != 0;
 }
 
-size_t pad_table_bytes(const SolveLaunch& a, int precision) {  // of one table (a few values read past the last row's end)
-    return ((size_t)a.P * a.pad_ld + 8) * (precision == RT_F64 ? 8 : 4);
+size_t pad_table_bytes(const SolveLaunch& a, int precision) {  // of one table (the last window ends with the last row)
+    return (size_t)a.P * a.pad_ld * (precision == RT_F64 ? 8 : 4);
 }
 
 hipError_t launch_pad(const SolveLaunch& a, int precision, hipStream_t s) {

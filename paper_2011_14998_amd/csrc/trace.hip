@@ -185,10 +185,12 @@ __global__ __launch_bounds__(256) void k_check_off(const int64_t* __restrict__ o
 // group evaluates the rule itself in FP64 over those that are left (exact_step).
 // The lists are those of the FP64 rule, bit for bit.
 //
-// What bounds it: VALU issue, ~170 instructions per step of a wave's 16 rays
-// (17 FP32 ones per candidate; the rule in FP64 takes ~20, most of them at
-// half rate), next to the row loads' latency (95 VGPRs, 5 waves per SIMD; 6
-// waves spill and are 3% slower).  Branch-free loads matter: lanes past their
+// What bounds it: the L1's data path and VALU issue side by side, both full:
+// the path returns data in 0.98 of the cycles on the cloud below, 0.97 on the grid
+// and 0.98 on the octree (TD busy), and each SIMD issues one VALU instruction per 4
+// cycles (~170 per step of a wave's 16 rays, 17 per candidate in FP32; the rule in
+// FP64 takes ~20).  95 VGPRs, 5 waves per SIMD; 6 waves spill and are 3% slower.
+// Branch-free loads matter: lanes past their
 // row's end read blank records, and whether a wave takes a fifth or sixth
 // piece is a scalar branch; loads under exec masks made the compiler wait for
 // some before it issued the rest (7.9 ms).  50 000-point cloud, 96 pairs,
