@@ -1287,24 +1287,53 @@ __global__ __launch_bounds__(256) void k_normalize8(const float* __restrict__ fe
 
 // Points p0 .. p0+n_points-1 (J1, Y and J start at point p0).
 // G lanes (a power of two up to 64) take a point, frequencies side by side; as one thread per point
-// every access of a wave was to 64 rows (65536 points of 64 frequencies 110 -> 17 us).
-__global__ __launch_bounds__(256) void k_closure_apply(const float* __restrict__ J1, const float* __restrict__ Y,
-                                                       int64_t n_points, int64_t F, int G, float log_bound,
-                                                       float* __restrict__ J, int32_t* __restrict__ flagged,
-                                                       int32_t* __restrict__ n_flagged, int64_t p0) {
+// every access of a wave was to 64 rows.  A workgroup takes APPLY_THREADS / G points at a time, `passes`
+// times (at most APPLY_THREADS points), and adds its flagged points to the counter at once: additions
+// to one address go through one by one, 10 ns each.  65536 points of 64 frequencies, none and all of them
+// flagged: 14.7 and 19.2 us (one thread per point, an addition per wave 128 and 129, G lanes and an
+// addition per point 17 and 750; workgroups of 256, eight on a CU 14.6 and 36).
+constexpr int APPLY_THREADS = 1024;
+__global__ __launch_bounds__(APPLY_THREADS) void k_closure_apply(const float* __restrict__ J1,
+                                                                 const float* __restrict__ Y, int64_t n_points,
+                                                                 int64_t F, int G, int passes, float log_bound,
+                                                                 float* __restrict__ J, int32_t* __restrict__ flagged,
+                                                                 int32_t* __restrict__ n_flagged, int64_t p0) {
+    __shared__ uint8_t is_flagged[APPLY_THREADS];
+    __shared__ int count[APPLY_THREADS / 64], base;
     const int l = threadIdx.x & (G - 1), first = (threadIdx.x & 63) & ~(G - 1);  // the point's lanes of the wave
-    for (int64_t i0 = blockIdx.x * (int64_t)256; i0 < n_points * G; i0 += (int64_t)gridDim.x * 256) {
-        const int64_t p = (i0 + threadIdx.x) / G;
-        bool fl = false;
-        if (p < n_points)
-            for (int64_t f = l; f < F; f += G) {
-                const int64_t i = p * F + f;
-                J[i] = J1[i] * __expf(Y[2 * i]);
-                fl = fl || (0.5f * Y[2 * i + 1] > log_bound);
-            }
-        uint64_t any = __builtin_amdgcn_ballot_w64(fl) >> first;
-        if (G < 64) any &= (1ull << G) - 1;
-        if (l == 0 && any) flagged[atomicAdd(n_flagged, 1)] = (int32_t)(p0 + p);
+    const int per = APPLY_THREADS / G, points = per * passes;
+    for (int64_t b0 = blockIdx.x * (int64_t)points; b0 < n_points; b0 += (int64_t)gridDim.x * points) {
+        for (int j = 0; j < passes; ++j) {
+            const int k = j * per + threadIdx.x / G;
+            const int64_t p = b0 + k;
+            bool fl = false;
+            if (p < n_points)
+                for (int64_t f = l; f < F; f += G) {
+                    const int64_t i = p * F + f;
+                    J[i] = J1[i] * __expf(Y[2 * i]);
+                    fl = fl || (0.5f * Y[2 * i + 1] > log_bound);
+                }
+            uint64_t any = __builtin_amdgcn_ballot_w64(fl) >> first;
+            if (G < 64) any &= (1ull << G) - 1;
+            if (l == 0) is_flagged[k] = any != 0;
+        }
+        __syncthreads();
+        const bool mine = (int)threadIdx.x < points && is_flagged[threadIdx.x];
+        const uint64_t m = __builtin_amdgcn_ballot_w64(mine);
+        const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+        if (lane == 0) count[wave] = (int)__popcll(m);
+        __syncthreads();
+        if (threadIdx.x == 0) {
+            int n = 0;
+            for (int w = 0; w < APPLY_THREADS / 64; ++w) n += count[w];
+            base = n ? atomicAdd(n_flagged, n) : 0;
+        }
+        __syncthreads();
+        if (mine) {
+            int at = base + (int)__popcll(m & ((1ull << lane) - 1));
+            for (int w = 0; w < wave; ++w) at += count[w];
+            flagged[at] = (int32_t)(p0 + b0 + threadIdx.x);
+        }
     }
 }
 
@@ -1685,8 +1714,12 @@ static void launch_apply(const float* J1, const float* Y, int64_t n_points, int6
                          int32_t* flagged, int32_t* n_flagged, int64_t p0, hipStream_t s) {
     int G = 1;
     while (G < 64 && G < F) G *= 2;
-    hipLaunchKernelGGL(k_closure_apply, dim3(capped_blocks((n_points * G + 255) / 256)), dim3(256), 0, s, J1, Y, n_points, F, G, log_bound,
-                       J, flagged, n_flagged, p0);
+    const int64_t groups = (n_points * G + APPLY_THREADS - 1) / APPLY_THREADS;
+    // one round of workgroups, two on every CU (rounded up: a workgroup too many would run by itself)
+    const int64_t full = (groups + 2 * num_cus() - 1) / (2 * num_cus());
+    const int passes = (int)(full < 1 ? 1 : full < G ? full : G);
+    hipLaunchKernelGGL(k_closure_apply, dim3(capped_blocks((groups + passes - 1) / passes)), dim3(APPLY_THREADS), 0, s,
+                       J1, Y, n_points, F, G, passes, log_bound, J, flagged, n_flagged, p0);
 }
 
 static void launch_normalize(const float* feat, int64_t n, const Norm& nm, uint16_t* X, hipStream_t s) {
