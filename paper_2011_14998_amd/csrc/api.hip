@@ -361,9 +361,10 @@ rt_status rt::model_create(const double* pos, int64_t P, const int64_t* nbr_off,
         }
         if (e == hipSuccess) e = hipMalloc(&ws, build_rows_workspace(P));
         if (e == hipSuccess) e = launch_build_rows(m, key, lay_d, ws, s);
-        uint64_t axial = 0;
-        if (e == hipSuccess) e = hipMemcpyAsync(&axial, ws, sizeof(axial), hipMemcpyDeviceToHost, s);
+        uint64_t parts[AXIAL_COUNTERS * AXIAL_STRIDE] = {}, axial = 0;
+        if (e == hipSuccess) e = hipMemcpyAsync(parts, ws, sizeof(parts), hipMemcpyDeviceToHost, s);
         if (e == hipSuccess) e = hipStreamSynchronize(s);
+        for (int i = 0; i < AXIAL_COUNTERS; ++i) axial += parts[i * AXIAL_STRIDE];
         m->lattice = E > 0 && axial >= (uint64_t)(E + 15) / 16;
         if (lay_d) (void)hipFree(lay_d);
         if (ws) (void)hipFree(ws);

@@ -155,7 +155,9 @@ enum RowLayout { ROWS_BY_SIZE = 0, ROWS_FAR = 1, ROWS_WIDE = 2 };
 size_t plan_rows(RowTab& tab, int64_t P, int64_t E, int layout);
 // Rows of a checked model, laid out in the point order `lay` (device [P], NULL: point
 // order), each in ascending key[id] (key NULL: ascending id); ws: build_rows_workspace(P) bytes, whose
-// first 8 then hold the number of edges along an axis.
+// first AXIAL_BYTES then hold the number of edges along an axis: AXIAL_COUNTERS 64-bit parts of it, a cache line each.
+constexpr int AXIAL_COUNTERS = 64, AXIAL_STRIDE = 16;
+constexpr size_t AXIAL_BYTES = sizeof(uint64_t) * AXIAL_COUNTERS * AXIAL_STRIDE;
 size_t build_rows_workspace(int64_t P);
 hipError_t launch_build_rows(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s);
 // `order` (optional): spatially sorted permutation of origin positions; the

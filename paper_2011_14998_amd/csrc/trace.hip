@@ -72,7 +72,8 @@ __global__ __launch_bounds__(256) void k_layout_codes(const int64_t* __restrict_
 // id, or in ascending key[id] when a key is given (equal keys in list order).  The walk
 // relies on that order: equal distances go to the earlier record.  The row's last unit is
 // filled up with blank records.  The model has been checked, so every index is in range.
-// *axial: the edges along an axis.
+// axial: the edges along an axis, in AXIAL_COUNTERS parts (additions to one address go through one by one:
+// 507 557 leaves of an octree 1.53 ms with a single one, 0.29 with none).
 constexpr int BUILD_LANES = 16;
 
 __global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ pos, int64_t P,
@@ -123,7 +124,7 @@ __global__ __launch_bounds__(256) void k_build_rows(const double* __restrict__ p
         along += __shfl_xor(along, o, BUILD_LANES);
     }
     if (sub == 0) {
-        if (along) atomicAdd(axial, (unsigned long long)along);
+        if (along) atomicAdd(axial + (blockIdx.x & (AXIAL_COUNTERS - 1)) * AXIAL_STRIDE, (unsigned long long)along);
         // never below the longest edge
         *(RowHead*)row = RowHead{x, y, z, (int32_t)p, (float)(longest * 1.000001)};
         if (!counted) rec[-1] = blank_rec((uint32_t)n);
@@ -708,18 +709,18 @@ size_t plan_rows(RowTab& t, int64_t P, int64_t E, int layout) {
 }
 
 size_t build_rows_workspace(int64_t P) {
-    return 256 + al256(sizeof(int32_t) * (size_t)P) + al256(sizeof(int64_t) * (size_t)(P + 1)) + al256(scan_workspace(P));
+    return AXIAL_BYTES + al256(sizeof(int32_t) * (size_t)P) + al256(sizeof(int64_t) * (size_t)(P + 1)) + al256(scan_workspace(P));
 }
 
 hipError_t launch_build_rows(const rt_model* m, const int32_t* key, const int32_t* lay, void* ws, hipStream_t s) {
-    int32_t* units = (int32_t*)((char*)ws + 256);
+    int32_t* units = (int32_t*)((char*)ws + AXIAL_BYTES);
     int64_t* start = (int64_t*)((char*)units + al256(sizeof(int32_t) * (size_t)m->P));
     void* scan_ws = (char*)start + al256(sizeof(int64_t) * (size_t)(m->P + 1));
     const unsigned g = (unsigned)blocks_for(m->P, 256);
     hipLaunchKernelGGL(k_layout_units, dim3(g), dim3(256), 0, s, m->off, lay, m->P, m->tab.sh, m->tab.nb,
                        units);
     hipError_t e = launch_scan(units, m->P, start, scan_ws, s);
-    if (e == hipSuccess) e = launch_fill_i32((int32_t*)ws, 2, 0, s);
+    if (e == hipSuccess) e = launch_fill_i32((int32_t*)ws, AXIAL_BYTES / sizeof(int32_t), 0, s);
     if (e != hipSuccess) return e;
     hipLaunchKernelGGL(k_layout_codes, dim3(g), dim3(256), 0, s, start, m->off, lay, m->P, m->tab.nb,
                        (int64_t)(ROW_BLANK >> m->tab.sh), m->codes);
