@@ -1070,7 +1070,9 @@ __global__ __launch_bounds__(256) void k_train_step(const float* __restrict__ bp
 // -> 159.  The distances come first, so calls too small to hide their latency pay
 // for it: summed by lane reads and in unrolled loads, 1000 points of 16
 // frequencies take 17.0 us (18.4 by shuffles, 16.8 in one loop with the rest);
-// unrolled by 8 the kernel loses two waves per SIMD.
+// unrolled by 8 the kernel loses two waves per SIMD.  Lanes side by side take them where the
+// workgroup has up to 64 points (60000 points of 31 frequencies, 14 and 100 neighbours: 140 and 995 us by
+// a thread per point, 125 and 906 so, 153 and 902 in one loop with the rest).
 constexpr int LOG_CACHE = 20;  // 20 KB of LDS: seven workgroups per CU; a mesh point has 15 neighbours on average
 template <bool WIDE>
 __global__ __launch_bounds__(256) void k_features(const double* __restrict__ pos, const int64_t* __restrict__ off,
@@ -1111,6 +1113,19 @@ __global__ __launch_bounds__(256) void k_features(const double* __restrict__ pos
                 }
             }
             if ((t & 63) == 0) sL[c] = (float)(L / (double)(e1 - e0));
+        }
+    } else if (np <= 64) {  // G lanes per point, summed in their neighbours' order (past the row's end: + 0)
+        const int G = np <= 16 ? 16 : np <= 32 ? 8 : 4, c = t / G;
+        const int64_t p = c < np ? point(k0 + c) : -1;
+        if (p >= 0) {
+            const int64_t e0 = off[p], e1 = off[p + 1];
+            double L = 0.0;
+            for (int64_t e = e0 + (t & (G - 1)); e - (t & (G - 1)) < e1; e += G) {
+                const double d = e < e1 ? dist(p, e) : 0.0;
+#pragma unroll 4
+                for (int l = 0; l < G; ++l) L += __shfl(d, l, G);
+            }
+            if ((t & (G - 1)) == 0) sL[c] = (float)(L / (double)(e1 - e0));
         }
     } else if (t < np) {
         const int64_t p = point(k0 + t);
